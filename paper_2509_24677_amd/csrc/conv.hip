@@ -3,6 +3,8 @@
 // Output-stationary gather-GEMM: a tile of output rows loops over the 27 offsets, gathers the
 // neighbour rows of each offset and multiplies them by W_k.  Each offset really is a dense
 // [rows x Cin] x [Cin x Cout] contraction, so the BF16 path runs it on MFMA.
+#include <type_traits>
+
 #include "conv_common.hpp"
 
 namespace npvs {
@@ -77,106 +79,274 @@ __global__ void pack_batch_kernel(PackBatch PB, int dtype) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Plain FP32 path (vector FMA).  Workgroup of 256 = 4 waves; a tile of 32 output rows; blockIdx.y
-// selects 64 output channels; lane = output channel, each wave owns 8 rows.  A tile is a
-// sequence of steps (offset k, 64-channel input chunk c0): the step's 32 gathered rows and its
-// 64 x 64 weight block go through LDS, every lane reading the rows as broadcasts and its weight
-// column without conflicts.  The loads of step s + 1 are issued into registers before the
-// products of step s, and the neighbour indices of offset k + 2 when offset k begins, so a step
-// waits for memory only when its products are shorter than a load.  The products run in the
-// order (offset, channel) for every output, so the result does not depend on the launch shape.
+// FP32 path on MFMA (v_mfma_f32_16x16x4_f32: float32 operands and accumulation), any channel
+// counts.  A workgroup of NW waves computes 16 MB rows x 16 NI outputs; the contraction over
+// (offset, input channel) is cut into substeps of 16 channels of one offset, dealt to the waves in
+// turn, so a wave's rows and weights are its own and nothing is shared (no barrier) until the NW
+// partial results are added in LDS in a fixed order.  The product is computed transposed
+// (D = W^T X^T).  The channels of a substep are taken in the order 4 g + j (lane group g = l / 16,
+// product j) and output block i holds the outputs NI m + i, so that every load is as wide as the
+// loader takes it (a load costs one cycle per 4 lanes whatever their width):
+//   A (16 x 4): lane l gives W[k][16 cc + 4 g + j][NI (l%16) + i]   one NI-word load serves NI blocks
+//   B (4 x 16): lane l gives X[row l%16][16 cc + 4 g + j]            one 16-byte LDS read serves 4 products
+//   D: lane l holds the 4 NI consecutive outputs from 4 NI g on of row l%16
+// The gathered rows go through LDS (wave-private, two buffers) because the operand layout puts
+// adjacent lanes on different rows, which loads at 67 cycles a KB against 26 with four adjacent
+// lanes on one row's 64 bytes.  LDS serves a wave's accesses in order, and lane 0 writes and reads
+// the same words, so the compiler keeps their order too.  Rows are loaded two substeps ahead,
+// indices three, weights one.
+// Bound by the matrix cores: the busiest compute unit of the 9 699-row 64 -> 64 layer has 1 296
+// products of 32 cycles per SIMD, 17 us of its 32.6 (113 us with vector FMA; without any load the
+// same loop takes 25), the rest being the launch and the first index, row and weight round trips.
 // ------------------------------------------------------------------------------------------
-constexpr int kF32Rows = 32;
+// All ones when ok, as a value whose origin the compiler does not see: a mask on a loaded value
+// (or on its index) then stays a mask, instead of becoming a branch around the load.
+__device__ __forceinline__ uint32_t lane_mask(bool ok) {
+  uint32_t m = ok ? ~0u : 0u;
+  asm volatile("" : "+v"(m));
+  return m;
+}
+__device__ __forceinline__ float and_mask(float v, uint32_t m) {
+  return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) & m);
+}
 
-__global__ __launch_bounds__(256) void conv_fwd_f32_kernel(const float *__restrict__ X, int cin,
-                                                            const float *__restrict__ P,
-                                                            const float *__restrict__ bias, int cout,
-                                                            const int32_t *__restrict__ nbr,
-                                                            const npvs_counts *__restrict__ counts, int cap, int relu,
-                                                            float *__restrict__ Y) {
-  __shared__ __align__(16) float Xs[kF32Rows][64];
-  __shared__ __align__(16) float Ws[64][64];
-  __shared__ int idx_s[2][kF32Rows];  // neighbour indices of offsets k (slot k % 2)
-  const int32_t n = counts->n_sites;
-  const int ntiles = (n + kF32Rows - 1) / kF32Rows;
-  const int tid = threadIdx.x, lane = tid & 63;
+// LDS: two buffers of rows per wave (64 bytes a row), later half of the waves' partial results
+// (16 MB rows of 16 NI + 4 floats, the 4 against bank conflicts)
+constexpr int f32_lds_words(int MB, int NI, int NW) {
+  const int rows = NW * 2 * 16 * MB * 4, part = NW / 2 * 16 * MB * (4 * NI + 1);
+  return rows > part ? rows : part;  // 16-byte words
+}
+
+// How the weights and rows may be read: kF32Full: cin % 16 == 0, cout % (16 NI) == 0; kF32Vec:
+// cin % 4 == 0, cout % NI == 0 (whole vectors, some of them outside); kF32Any: word by word.
+enum F32Access { kF32Full, kF32Vec, kF32Any };
+
+template <int N> struct FloatVec { float v[N]; };
+
+template <int MB, int NI, int NW, F32Access ACC>
+__device__ __forceinline__ void conv_f32_body(float4 *lds, const float *__restrict__ X, int cin,
+                                              const float *__restrict__ P, const float *__restrict__ bias, int cout,
+                                              const int32_t *__restrict__ nbr, int n, int cap, int relu,
+                                              float *__restrict__ Y) {
+  constexpr int ROWS = 16 * MB, RP = 4 * NI + 1;  // RP: 16-byte words per partial row
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, m = lane & 15;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform (scalar)
-  const int cg = 64 * blockIdx.y, o = cg + lane;
-  const int CB = (cin + 63) / 64, S = 27 * CB;  // steps per tile
+  const int C16 = (cin + 15) / 16, U = 27 * C16, S = (U - wv + NW - 1) / NW;  // substeps wv, wv + NW, ...
+  const int kq = NW / C16, cq = NW % C16;  // the advance in (offset, 16-channel chunk) per substep of a wave
+  const int ntiles = (n + ROWS - 1) / ROWS, groups = (cout + 16 * NI - 1) / (16 * NI), nunits = ntiles * groups;
+  float4 *rows = lds + wv * 2 * ROWS * 4;
+  // word q of row r sits at slot q ^ swz(r): the 8 (or 16) lanes of one LDS pass, on consecutive
+  // rows at one q, then fall on different banks
+  auto swz = [](int r) { return ((r >> 1) ^ (r >> 3)) & 3; };
   for (int j = 0;; ++j) {
-    const int tile = xcd_tile(blockIdx.x, gridDim.x, ntiles, j);
-    if (tile < 0) break;
-    const int row0 = tile * kF32Rows;
-    auto idx_load = [&](int k) {
-      return tid < kF32Rows && row0 + tid < n ? nbr[(int64_t)k * cap + row0 + tid] : -1;
-    };
-    float xr[8], wr[16];
-    auto load_step = [&](int s) {  // step s's rows (through the indices in LDS) and weights
-      const int k = s / CB, c0 = (s - k * CB) * 64;
-      const int *ids = idx_s[k & 1];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int e = tid + 256 * u, r = e >> 6, c = c0 + (e & 63), src = ids[r];
-        xr[u] = src >= 0 && c < cin ? X[(int64_t)src * cin + c] : 0.0f;
-      }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int e = tid + 256 * u, c = c0 + (e >> 6), oo = cg + (e & 63);
-        wr[u] = c < cin && oo < cout ? P[((int64_t)k * cin + c) * cout + oo] : 0.0f;
+    const int unit = xcd_tile(blockIdx.x, gridDim.x, nunits, j);
+    if (unit < 0) break;
+    const int row0 = unit / groups * ROWS, o0 = unit % groups * 16 * NI, o = o0 + NI * m;
+    int k = wv / C16, cc = wv % C16;   // (offset, chunk) of the index loads
+    int wk = k, wc = cc;               // and of the weight loads
+    auto advance = [&](int &a, int &b) {
+      a += kq;
+      b += cq;
+      if (b >= C16) {
+        b -= C16;
+        ++a;
       }
     };
-    auto store_step = [&]() {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) Xs[(tid + 256 * u) >> 6][tid & 63] = xr[u];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) Ws[(tid + 256 * u) >> 6][tid & 63] = wr[u];
+    // Loads retire in order, so a value used right after its load makes every earlier load wait:
+    // indices, rows and weights are loaded raw and judged where they are used.  Loads past the
+    // last substep re-read valid places and are not used.
+    struct Index {
+      int i[MB], c;  // raw indices and the channel they are for
     };
-    if (tid < kF32Rows) {
-      idx_s[0][tid] = idx_load(0);
-      idx_s[1][tid] = idx_load(1);
-    }
-    __syncthreads();
-    load_step(0);
-    store_step();
-    __syncthreads();
-    float acc[8];
+    auto next_index = [&]() {
+      Index ix;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = 0.0f;
-    int ni = -1;  // indices of offset k + 2, loaded when offset k begins
-    for (int s = 0; s < S; ++s) {
-      const int k = s / CB, cb = s - k * CB, c0 = cb * 64;
-      if (cb == 0 && k + 2 < 27) ni = idx_load(k + 2);
-      if (s + 1 < S) load_step(s + 1);
-      const int cn = ((cin - c0 < 64 ? cin - c0 : 64) + 3) & ~3;  // entries past cin are zero
-      for (int c = 0; c < cn; c += 4) {
-        const float w0 = Ws[c][lane], w1 = Ws[c + 1][lane], w2 = Ws[c + 2][lane], w3 = Ws[c + 3][lane];
+      for (int u = 0; u < MB; ++u) {
+        const int r = row0 + 16 * u + (lane >> 2);
+        ix.i[u] = nbr[(int64_t)(k < 27 ? k : 26) * cap + (r < n ? r : n - 1)];
+      }
+      ix.c = 16 * cc + 4 * (lane & 3);
+      advance(k, cc);
+      return ix;
+    };
+    auto load_rows = [&](const Index &ix, float4 (&x)[MB], int (&left)[MB]) {  // left: how many of the channels exist
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float4 xv = *reinterpret_cast<const float4 *>(&Xs[wv * 8 + i][c]);
-          acc[i] = fmaf(xv.x, w0, acc[i]);
-          acc[i] = fmaf(xv.y, w1, acc[i]);
-          acc[i] = fmaf(xv.z, w2, acc[i]);
-          acc[i] = fmaf(xv.w, w3, acc[i]);
+      for (int u = 0; u < MB; ++u) {
+        left[u] = ix.i[u] >= 0 && row0 + 16 * u + (lane >> 2) < n ? cin - ix.c : 0;
+        const float *src = X + (left[u] > 0 ? (int64_t)ix.i[u] * cin + ix.c : 0);
+        if constexpr (ACC != kF32Any) {
+          x[u] = *reinterpret_cast<const float4 *>(src);
+        } else {
+          x[u].x = src[0];
+          x[u].y = src[lane_mask(left[u] > 1) & 1u];
+          x[u].z = src[lane_mask(left[u] > 2) & 2u];
+          x[u].w = src[lane_mask(left[u] > 3) & 3u];
         }
       }
-      __syncthreads();  // the products of step s are done with Xs and Ws
-      if (s + 1 < S) store_step();
-      // offset k's indices were last read by the loads of its last step, issued during step s
-      if (cb == CB - 1 && k + 2 < 27 && tid < kF32Rows) idx_s[k & 1][tid] = ni;
-      __syncthreads();
-    }
-    if (o < cout) {
-      const float bo = bias ? bias[o] : 0.0f;
+    };
+    auto store_rows = [&](int buf, const float4 (&x)[MB], const int (&left)[MB]) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int r = row0 + wv * 8 + i;
-        if (r < n) {
-          const float v = acc[i] + bo;
-          Y[(int64_t)r * cout + o] = (relu && v < 0.0f) ? 0.0f : v;
+      for (int u = 0; u < MB; ++u) {
+        const int r = 16 * u + (lane >> 2);
+        const uint32_t m0 = lane_mask(left[u] > 0), m1 = ACC != kF32Any ? m0 : lane_mask(left[u] > 1),
+                       m2 = ACC != kF32Any ? m0 : lane_mask(left[u] > 2),
+                       m3 = ACC != kF32Any ? m0 : lane_mask(left[u] > 3);
+        rows[(buf * ROWS + r) * 4 + ((lane & 3) ^ swz(r))] =
+            make_float4(and_mask(x[u].x, m0), and_mask(x[u].y, m1), and_mask(x[u].z, m2), and_mask(x[u].w, m3));
+      }
+    };
+    auto load_weights = [&](float (&w)[4][NI], int &left) {  // left: of the channels from 4 g on, how many exist
+      const int c = 16 * wc + 4 * g;
+      left = o < cout ? cin - c : 0;
+      const bool any = ACC == kF32Full || left > 0;
+      const float *src = P + (any ? ((int64_t)(wk < 27 ? wk : 26) * cin + c) * cout + o : 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float *s = src + (ACC == kF32Full ? (uint32_t)(q * cout) : (uint32_t)(q * cout) & lane_mask(left > q));
+        if constexpr (ACC == kF32Any || NI == 1) {
+#pragma unroll
+          for (int i = 0; i < NI; ++i) w[q][i] = s[i == 0 ? 0u : (uint32_t)i & lane_mask(o + i < cout)];
+        } else {
+          FloatVec<NI> v;
+          __builtin_memcpy(&v, s, sizeof(v));
+#pragma unroll
+          for (int i = 0; i < NI; ++i) w[q][i] = v.v[i];
         }
       }
+      advance(wk, wc);
+    };
+    f32x4_t acc[MB][NI];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int i = 0; i < NI; ++i) acc[mb][i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    float4 x[2][MB];
+    float w[2][4][NI];
+    int xl[2][MB], wl[2];
+    const Index ix0 = next_index(), ix1 = next_index();
+    Index ix = next_index();
+    load_weights(w[0], wl[0]);
+    load_rows(ix0, x[0], xl[0]);
+    load_rows(ix1, x[1], xl[1]);
+    store_rows(0, x[0], xl[0]);
+    // substep s (parity cur): its rows are in LDS, those of the next in x[cur ^ 1], indices two ahead in ix
+    auto step = [&](auto parity) {
+      constexpr int cur = decltype(parity)::value;
+      load_rows(ix, x[cur], xl[cur]);
+      ix = next_index();
+      load_weights(w[cur ^ 1], wl[cur ^ 1]);
+      float4 b[MB];
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) b[mb] = rows[(cur * ROWS + mb * 16 + m) * 4 + (g ^ swz(mb * 16 + m))];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t mq = ACC == kF32Full ? 0u : lane_mask(wl[cur] > q);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          float av = w[cur][q][i];
+          if constexpr (ACC == kF32Vec) av = and_mask(av, mq);
+          if constexpr (ACC == kF32Any) av = and_mask(av, mq & lane_mask(o + i < cout));
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) {
+            const float bv = q == 0 ? b[mb].x : q == 1 ? b[mb].y : q == 2 ? b[mb].z : b[mb].w;
+            acc[mb][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc[mb][i], 0, 0, 0);
+          }
+        }
+      }
+      store_rows(cur ^ 1, x[cur ^ 1], xl[cur ^ 1]);
+    };
+    for (int s = 1; s < S; s += 2) {
+      step(std::integral_constant<int, 0>{});
+      step(std::integral_constant<int, 1>{});
     }
+    if (S & 1) step(std::integral_constant<int, 0>{});
+    // the partial results: the upper half of the waves hand theirs to the lower half, then all
+    // threads add the sums of their 16-byte words in wave order
+    float4 *part = lds + (wv % (NW / 2)) * ROWS * RP;
+    auto word = [&](int mb, int f) {  // words f of the 4 NI consecutive outputs of this lane
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = acc[mb][(4 * f + e) % NI][(4 * f + e) / NI];
+      return make_float4(v[0], v[1], v[2], v[3]);
+    };
+    __syncthreads();  // every wave is done with its rows
+    if (wv >= NW / 2)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int f = 0; f < NI; ++f) part[(mb * 16 + m) * RP + g * NI + f] = word(mb, f);
+    __syncthreads();
+    if (wv < NW / 2)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int f = 0; f < NI; ++f) {
+          float4 *p = part + (mb * 16 + m) * RP + g * NI + f;
+          const float4 a = word(mb, f), b = *p;
+          *p = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+        }
+    __syncthreads();
+    for (int e = tid; e < ROWS * 4 * NI; e += 64 * NW) {
+      const int rr = e / (4 * NI), f = e % (4 * NI), r = row0 + rr, oo = o0 + 4 * f;
+      if (r >= n || oo >= cout) continue;
+      float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int s = 0; s < NW / 2; ++s) {
+        const float4 p = lds[(s * ROWS + rr) * RP + f];
+        v[0] += p.x;
+        v[1] += p.y;
+        v[2] += p.z;
+        v[3] += p.w;
+      }
+      float *dst = Y + (int64_t)r * cout + oo;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (ACC != kF32Full && oo + i >= cout) break;
+        const float t = v[i] + (bias ? bias[oo + i] : 0.0f);
+        dst[i] = (relu && t < 0.0f) ? 0.0f : t;
+      }
+    }
+    __syncthreads();  // before the next unit's rows
   }
+}
+
+// Rows per workgroup: 48, which read the weights a third as often as 16, when that takes no more
+// rounds over the 256 compute units than 16 do, or when there are enough units (two a compute unit)
+// that rounds do not matter.  64 -> 64: 9 699 rows 32.6 us (16 rows: 35.6), 94 371 rows 211 (247);
+// 1 802 rows 14.8 us with 16 (48 rows: 30.5).
+template <int NI, int NW, F32Access ACC>
+__global__ __launch_bounds__(64 * NW, ACC == kF32Any ? 2 : 3) void conv_fwd_f32_kernel(const float *__restrict__ X, int cin,
+                                                                const float *__restrict__ P,
+                                                                const float *__restrict__ bias, int cout,
+                                                                const int32_t *__restrict__ nbr,
+                                                                const npvs_counts *__restrict__ counts, int cap,
+                                                                int relu, float *__restrict__ Y) {
+  __shared__ float4 lds[f32_lds_words(3, NI, NW)];
+  const int32_t n = counts->n_sites;
+  const int groups = (cout + 16 * NI - 1) / (16 * NI);
+  const int64_t t1 = (n + 15) / 16 * (int64_t)groups, t3 = (n + 47) / 48 * (int64_t)groups;
+  if (t3 >= 512 || 3 * ((t3 + 255) / 256) <= (t1 + 255) / 256)
+    conv_f32_body<3, NI, NW, ACC>(lds, X, cin, P, bias, cout, nbr, n, cap, relu, Y);
+  else
+    conv_f32_body<1, NI, NW, ACC>(lds, X, cin, P, bias, cout, nbr, n, cap, relu, Y);
+}
+
+template <int NI>
+static void launch_conv_f32(const float *X, int cin, const float *P, const float *bias, int cout, const int32_t *nbr,
+                            const npvs_counts *counts, int cap, int relu, float *Y, hipStream_t s) {
+  const int64_t units = (int64_t)((cap + 15) / 16) * ((cout + 16 * NI - 1) / (16 * NI));
+  const int G = units > 2048 ? 2048 : (int)((units + 7) & ~7);
+  const bool vec = cin % 4 == 0 && cout % NI == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+  // 4 waves (three workgroups a compute unit hide each other's start and end), or 8 from 256 input
+  // channels on, where a wave's chain is long and the sites are few (512 -> 64, 1 802 rows: 80 us
+  // against 104; 64 -> 64, 94 371 rows: 232 against 211)
+#define NPVS_F32_LAUNCH(NW, ACC) \
+  conv_fwd_f32_kernel<NI, NW, ACC><<<G, 64 * NW, 0, s>>>(X, cin, P, bias, cout, nbr, counts, cap, relu, Y)
+  if (!vec) NPVS_F32_LAUNCH(4, kF32Any);
+  else if (cin % 16 || cout % (16 * NI)) NPVS_F32_LAUNCH(4, kF32Vec);
+  else if (cin >= 256) NPVS_F32_LAUNCH(8, kF32Full);
+  else NPVS_F32_LAUNCH(4, kF32Full);
+#undef NPVS_F32_LAUNCH
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1043,13 +1213,16 @@ npvs_status conv_fwd_dispatch(const void *X, int32_t cin, const void *Wp, const 
                               const int32_t *nbr, const npvs_counts *counts, int32_t cap, int32_t dtype, int32_t relu,
                               int32_t out_f32, void *Y, hipStream_t s, int variant, void *ws, size_t ws_bytes) {
   if (dtype == NPVS_F32) {
-    const int groups = (cout + 63) / 64;
-    int G = stride_grid(cap, kF32Rows, 2048);
-    const int most = 8192 / groups;  // workgroups over all output groups, at most about 8192
-    if (G > most) G = most;
-    G = G < 8 ? 8 : (G + 7) & ~7;
-    conv_fwd_f32_kernel<<<dim3(G, groups), 256, 0, s>>>((const float *)X, cin, (const float *)Wp, bias, cout, nbr,
-                                                         counts, cap, relu, (float *)Y);
+    // output blocks of 16 in groups of at most 4, as even as they divide
+    const int blocks = (cout + 15) / 16, per = (blocks + 3) / 4, NI = (blocks + per - 1) / per;
+    const float *Xf = static_cast<const float *>(X), *P = static_cast<const float *>(Wp);
+    float *Yf = static_cast<float *>(Y);
+    switch (NI) {
+      case 1: launch_conv_f32<1>(Xf, cin, P, bias, cout, nbr, counts, cap, relu, Yf, s); break;
+      case 2: launch_conv_f32<2>(Xf, cin, P, bias, cout, nbr, counts, cap, relu, Yf, s); break;
+      case 3: launch_conv_f32<3>(Xf, cin, P, bias, cout, nbr, counts, cap, relu, Yf, s); break;
+      default: launch_conv_f32<4>(Xf, cin, P, bias, cout, nbr, counts, cap, relu, Yf, s); break;
+    }
     return check_hip(hipGetLastError(), "npvs_sparse_conv_fwd");
   }
   if (cin % 8 || cout % 8)
