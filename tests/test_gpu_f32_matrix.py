@@ -1,9 +1,11 @@
 """FP32 layers on the matrix cores at the edges of their tiles: forward and data gradient (row
-tiles of 16 and 48, channel substeps of 16, output blocks of 16, vector and word access), against
-float64 sums over the same neighbour map.
+tiles of 16 and 48, channel substeps of 16, output blocks of 16, vector and word access) and weight
+gradient (chunks of 32 pairs, products of 4, narrow and ragged windows), against float64 sums over
+the same neighbour map.
 
-Tolerance: a float32 sum of N products in any order is within gamma_N sum |x||w| of the exact one;
-2 N 2^-24 covers it with the rounding of the result."""
+Tolerances: a float32 sum of N products in any order is within gamma_N sum |x||w| of the exact one;
+2 N 2^-24 covers it with the rounding of the result.  A weight-gradient entry is a compensated sum
+of plain sums of at most 32 products: 2 * 40 * 2^-24 sum |x||dz|."""
 import numpy as np
 import pytest
 import torch
@@ -65,3 +67,22 @@ def test_conv_fwd_f32_tiles(sites, cin, cout, offset):
         want = ref.clamp_min(0) if relu else ref
         err = (Y[:sites].double() - want).abs()
         assert bool((err <= 2 * (27 * cin + 2) * 2.0 ** -24 * mag).all()), float((err / mag).max())
+
+
+@pytest.mark.parametrize("sites,cin,cout,offset", [
+    (1, 64, 64, 0), (5, 8, 16, 0), (33, 16, 33, 0), (300, 1, 1, 0), (300, 3, 65, 0), (300, 64, 64, 1), (300, 17, 32, 0),
+    (300, 50, 16, 0), (300, 130, 20, 0), (4100, 32, 64, 0), (9699, 64, 64, 0)])
+def test_wgrad_f32_windows(sites, cin, cout, offset):
+    rb, nbr = rulebook(sites, sites, csr=True)
+    gen = torch.Generator(device=DEV).manual_seed(cin * 1000 + cout)
+    X = rows(sites, cin, rb.cap, gen, offset)
+    dY = rows(sites, cout, rb.cap, gen)
+    W = torch.randn((27, cin, cout), generator=gen, device=DEV)
+    _, dW, db = npvs.sparse_conv_bwd(X, npvs.pack_weights(W, npvs.NPVS_F32, True), cin, cout, None, dY, rb,
+                                     npvs.NPVS_F32, False, want_dx=False)
+    Xz, idx, dZ = padded(X, sites), torch.where(nbr < 0, sites, nbr), dY[:sites].double()
+    for k in range(27):
+        ref = Xz[idx[k]].T @ dZ
+        mag = Xz[idx[k]].abs().T @ dZ.abs()
+        err = (dW[k].double() - ref).abs()
+        assert bool((err <= 80 * 2.0 ** -24 * mag).all()), (k, float((err / mag.clamp_min(1e-30)).max()))
