@@ -85,8 +85,8 @@ __global__ __launch_bounds__(256) void relu_grad_kernel(const T *__restrict__ Y,
         if (dZ32) *reinterpret_cast<f32x4_t *>(dZ32 + e) = o;
         if (dZ16) {
           uint2 h;
-          h.x = (uint32_t)f32_to_bf16(g[0]) | ((uint32_t)f32_to_bf16(g[1]) << 16);
-          h.y = (uint32_t)f32_to_bf16(g[2]) | ((uint32_t)f32_to_bf16(g[3]) << 16);
+          h.x = f32x2_to_bf16(g[0], g[1]);
+          h.y = f32x2_to_bf16(g[2], g[3]);
           *reinterpret_cast<uint2 *>(dZ16 + e) = h;
         }
       }

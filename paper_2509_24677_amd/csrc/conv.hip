@@ -760,8 +760,8 @@ __device__ __forceinline__ void wsta_body(const uint16_t *__restrict__ X, int ci
 #pragma unroll
           for (int i = 0; i < 4; ++i) da[i] += g[i];
           uint2 h;
-          h.x = (uint32_t)f32_to_bf16(g[0]) | ((uint32_t)f32_to_bf16(g[1]) << 16);
-          h.y = (uint32_t)f32_to_bf16(g[2]) | ((uint32_t)f32_to_bf16(g[3]) << 16);
+          h.x = f32x2_to_bf16(g[0], g[1]);
+          h.y = f32x2_to_bf16(g[2], g[3]);
           *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(Y) + (int64_t)r * cout + o) = h;
         }
       } else if constexpr (BIAS_ONCE) {
@@ -797,6 +797,60 @@ __global__ __launch_bounds__(576) void conv_fwd_bf16_wsta_kernel(const uint16_t 
 // tiles later, after a barrier that every reducer reaches only once it has read the table.  The
 // twelve waves fill three per SIMD at up to 168 registers, as many as the nine-wave kernel's
 // register budget allows on the busiest SIMD.
+// The gathered rows reach a product wave through LDS.  The MFMA operand wants lane l on row l % 16,
+// and a load whose adjacent lanes lie on different rows takes one cycle per lane (67 cycles a KB),
+// so each load instead covers whole rows with adjacent lanes (26 cycles a KB) and goes straight to
+// a wave-private stage in LDS, one slot per offset; the operands are 16-byte LDS reads.  Everything
+// runs one step ahead: while the products of tile j take offset q's operands, the slot of offset q
+// (tile j + 1) is read into the same registers and then loaded again (tile j + 2), so the matrix
+// cores, the LDS and the loads are busy at the same time.  The waits are counted by hand (a load to
+// LDS has no register for the compiler to track); the product loop has no other load, because the
+// reducers fetch the neighbour indices, six tiles ahead, into a ring in LDS.  A missing neighbour
+// lies past the end of the row buffer and loads as zero, so no operand is masked.
+// Measured, 64 -> 64, against rows loaded straight into registers: 9 699 rows 7.9 us (8.8), 20 971
+// rows 11.3 (12.9), 140 078 rows 47.1 (51.8); 8 -> 64 on 49 283 rows 13.6 (15.5), 16 -> 16 on 819 rows
+// 3.3 (3.7); vector instructions of the large layer 4.8 M against 11.2 M.  On the large
+// layer the products of the SIMD with three product waves take 1 152 of a tile's 2 700 cycles, the
+// loads 1 215 and the LDS about 1 400, and the barrier of each tile lets them overlap only in part.
+template <int KB>
+struct RowStage {
+  static constexpr int LPR = 4 * KB;        // lanes (16-byte words) per row
+  static constexpr int RPL = 64 / LPR;      // rows per load
+  static constexpr int LOADS = 16 / RPL;    // loads per slot (16 rows of one offset)
+  static constexpr int SLOT = 16 * LPR;     // 16-byte words per slot
+  // word c of row r sits at place c ^ swz(r): the 8 lanes of one LDS pass, on consecutive rows at
+  // one c, then fall on different banks
+  static __device__ __forceinline__ int swz(int r) { return KB == 1 ? (r >> 1) & 3 : r & 7; }
+};
+
+// The rows X as a buffer of `bytes` bytes: a load past its end gives zero.
+typedef int32_t rsrc_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ rsrc_t row_buffer(const uint16_t *X, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(X);
+  return rsrc_t{(int32_t)(uint32_t)a, (int32_t)((uint32_t)(a >> 32) & 0xffffu), (int32_t)bytes, 0x00020000};
+}
+// Start loads to LDS address dst (wave-uniform, bytes), lane i's 16 bytes (4 bytes) to dst + 16 i (4 i).
+// No register is written: a load takes its LDS address from m0 and goes past the vector registers.
+__device__ __forceinline__ void buffer_to_lds16(rsrc_t buf, uint32_t off, uint32_t dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(buf) : "memory");
+}
+__device__ __forceinline__ void global_to_lds4(const int32_t *src, uint32_t dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(dst), "v"(src) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const void *p) {  // of a wave-uniform LDS pointer
+  return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p);
+}
+
+// At most N of this wave's vector memory operations still in flight (in order: all older ones done).
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// This wave's LDS reads are in registers.
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// A workgroup barrier that orders LDS only: unlike __syncthreads it does not wait for loads in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 template <int KB>
 __global__ __launch_bounds__(768) void conv_fwd_bf16_wsred_kernel(const uint16_t *__restrict__ X, int cin,
                                                                   const bf16x8_t *__restrict__ Wp,
@@ -805,18 +859,38 @@ __global__ __launch_bounds__(768) void conv_fwd_bf16_wsred_kernel(const uint16_t
                                                                   const npvs_counts *__restrict__ counts, int cap,
                                                                   int relu, int out_f32, void *__restrict__ Y) {
   constexpr int KSPLIT = 9, KPER = 3, ROWS = 16, NBLK = 4, NRED = 3;
+  constexpr int RING = 8, IDX = 512;  // ring slots; the 27 x 16 indices of a step, three loads of 64 a reducer
+  typedef RowStage<KB> S;
   __shared__ f32x4_t red[2][KSPLIT * NBLK * 64];
+  __shared__ uint4 stages[KSPLIT][KPER][S::SLOT];
+  __shared__ int ring[RING][IDX];  // the neighbour indices [27][16] of step T's tile in slot T % RING
   const int32_t n = counts->n_sites;
   const int ntiles = (n + ROWS - 1) / ROWS;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, uniform (scalar)
   const bool prod = wv < KSPLIT;                                     // a product wave (else a reducer)
-  const int kbeg = (prod ? wv : 0) * KPER, csub = 8 * (lane >> 4);
   const int NBT = (cout + 15) / 16;
-  int tile = xcd_tile(blockIdx.x, gridDim.x, ntiles, 0);
-  if (tile < 0) return;  // whole workgroup: tile depends on blockIdx only
-  bf16x8_t aw[KPER][KB][NBLK];
-  if (prod)
+  const int tile0 = xcd_tile(blockIdx.x, gridDim.x, ntiles, 0);
+  if (tile0 < 0) return;  // whole workgroup: tile depends on blockIdx only
+  auto tile_at = [&](int j) { return xcd_tile(blockIdx.x, gridDim.x, ntiles, j); };
+  // The two roles walk the same tiles in their own loops, one barrier per tile each (the role is
+  // uniform over a wave, so every wave of the workgroup meets every barrier).
+  if (prod) {
+    // The first tile's rows are loaded straight into the operand registers, through this wave's own
+    // index loads (a workgroup with one tile then needs nothing else); the second and third tiles'
+    // indices are loaded here too, lane 16 q + r holding offset q, row r.
+    const int kbeg = wv * KPER;
+    auto own_index = [&](int k, int t) {  // rows past the last site take its neighbours: not stored
+      const int r = t * ROWS + (lane & 15);
+      return nbr[(int64_t)(kbeg + k) * cap + (r < n ? r : n - 1)];
+    };
+    int i0[KPER], i12[2] = {0, 0};
+#pragma unroll
+    for (int q = 0; q < KPER; ++q) i0[q] = own_index(q, tile0);
+#pragma unroll
+    for (int j = 1; j < 3; ++j)
+      if (tile_at(j) >= 0) i12[j - 1] = own_index(lane < 48 ? lane >> 4 : 2, tile_at(j));
+    bf16x8_t aw[KPER][KB][NBLK];
 #pragma unroll
     for (int q = 0; q < KPER; ++q)
 #pragma unroll
@@ -826,104 +900,150 @@ __global__ __launch_bounds__(768) void conv_fwd_bf16_wsred_kernel(const uint16_t
           const int g = nb < NBT ? nb : NBT - 1;  // blocks past cout: any valid fragment
           aw[q][kb][nb] = Wp[(((int64_t)(kbeg + q) * NBT + g) * KB + kb) * 64 + lane];
         }
-  // as in the single-role kernel: indices and rows loaded raw, rows masked where the products
-  // read them (loads retire in order, so nothing loaded is used right after its load)
-  auto indices = [&](int t, int (&ix)[KPER]) {
+    // this lane's part of a slot's loads: rows t RPL + lane / LPR, always the same channels.  A
+    // missing row (index -1, 2^24 - 1 as the 24 bits multiplied) and channels past cin lie past
+    // the end of the buffer and load as zero.
+    const rsrc_t rows = row_buffer(X, (uint32_t)n * (uint32_t)(2 * cin));  // at most 2^31 bytes: n < 2^24
+    const int lr = lane / S::LPR, lc = 8 * ((lane % S::LPR) ^ S::swz(lr));
+    const uint32_t coff = lc < cin ? 2 * lc : 0x80000000u;
+    const uint32_t st0 = lds_address(stages[wv][0]);
+    int src[KPER][S::LOADS];  // the rows of the step to load next
+    auto indices = [&](int T) {
+      const int *rs = ring[T % RING] + kbeg * ROWS + lr;
 #pragma unroll
-    for (int q = 0; q < KPER; ++q) {
-      const int r = t * ROWS + (lane & 15);
-      ix[q] = nbr[(int64_t)(kbeg + q) * cap + (r < n ? r : n - 1)];
-    }
-  };
-  auto rows = [&](const int (&ix)[KPER], int t, uint4 (&b)[KPER][KB], uint32_t &m) {
-    m = 0u;
+      for (int q = 0; q < KPER; ++q)
 #pragma unroll
-    for (int q = 0; q < KPER; ++q) {
-      const bool ok = t * ROWS + (lane & 15) < n && ix[q] >= 0;
-      m |= (ok ? 1u : 0u) << q;
+        for (int t = 0; t < S::LOADS; ++t) src[q][t] = rs[q * ROWS + t * S::RPL];
+    };
+    auto spread = [&](int ix) {  // the same from an index register of the prologue
+#pragma unroll
+      for (int q = 0; q < KPER; ++q)
+#pragma unroll
+        for (int t = 0; t < S::LOADS; ++t)
+          src[q][t] = __builtin_amdgcn_ds_bpermute(4 * (q * ROWS + t * S::RPL + lr), ix);
+    };
+    auto load_slot = [&](int q) {
+#pragma unroll
+      for (int t = 0; t < S::LOADS; ++t)
+        buffer_to_lds16(rows, __umul24((uint32_t)src[q][t], 2 * cin) + coff, st0 + 16 * (q * S::SLOT + t * 64));
+    };
+    bf16x8_t bx[KPER][KB];
+    auto read_slot = [&](int q) {
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) {
-        const int c = kb * 32 + csub;
-        b[q][kb] = *reinterpret_cast<const uint4 *>(X + (ok && c < cin ? (int64_t)ix[q] * cin + c : 0));
+        const int r = lane & 15, c = 4 * kb + (lane >> 4);
+        bx[q][kb] = __builtin_bit_cast(bf16x8_t, stages[wv][q][r * S::LPR + (c ^ S::swz(r))]);
       }
-    }
-  };
-  // a reducer's blocks: wv - 9 and wv - 6 (the second only for wave 9); their bias, loaded once
-  float bv[2][4] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
-  if (!prod && bias)
+    };
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int blk = wv - KSPLIT + NRED * h, o = blk * 16 + 4 * (lane >> 4);
-      if (blk < NBLK && o < cout)
+    for (int q = 0; q < KPER; ++q)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) bv[h][i] = bias[o + i];
+      for (int kb = 0; kb < KB; ++kb) {
+        const int c = kb * 32 + 8 * (lane >> 4);
+        bx[q][kb] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(X), 0, n * 2 * cin, 0x00020000),
+            __umul24((uint32_t)i0[q], 2 * cin) + (c < cin ? 2 * c : 0x80000000u), 0, 0));
+      }
+    if (tile_at(1) >= 0) {
+      spread(i12[0]);
+#pragma unroll
+      for (int q = 0; q < KPER; ++q) load_slot(q);
+      spread(i12[1]);
     }
-  // The two roles walk the same tiles in their own loops, one barrier per tile each (the role is
-  // uniform over a wave, so every wave of the workgroup meets every barrier); in the reducers'
-  // loop no product registers are live, so a reducer loads all nine partials of its blocks at once.
-  int t1 = xcd_tile(blockIdx.x, gridDim.x, ntiles, 1);
-  if (prod) {
-    int ix[KPER];
-    uint4 bx[KPER][KB];
-    uint32_t bm = 0u;
-    indices(tile, ix);
-    rows(ix, tile, bx, bm);
-    indices(t1 >= 0 ? t1 : tile, ix);
-    for (int j = 0; tile >= 0; ++j) {
-      const int t2 = xcd_tile(blockIdx.x, gridDim.x, ntiles, j + 2);
-      f32x4_t *tab = red[j & 1];
+    // the weights and the first rows have landed: as the builtin, so that the compiler knows and
+    // puts no wait for them (which would count the stage's loads) into the loop
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
+    // step j, with src the rows of step j + 2; MORE: how many steps follow (0, 1, or 2 for more)
+    auto step = [&](int j, auto follow) {
+      constexpr int MORE = decltype(follow)::value;
       f32x4_t acc[NBLK];
 #pragma unroll
       for (int nb = 0; nb < NBLK; ++nb) acc[nb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int q = 0; q < KPER; ++q)
+      for (int q = 0; q < KPER; ++q) {
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-          const uint32_t mm = ((bm >> q) & 1u) && kb * 32 + csub < cin ? ~0u : 0u;
-          const uint4 v = bx[q][kb];
-          const uint4 row = make_uint4(v.x & mm, v.y & mm, v.z & mm, v.w & mm);
+        for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
           for (int nb = 0; nb < NBLK; ++nb)
-            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[q][kb][nb], __builtin_bit_cast(bf16x8_t, row),
-                                                              acc[nb], 0, 0, 0);
+            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[q][kb][nb], bx[q][kb], acc[nb], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (MORE > 0) {
+          wait_lds();  // slot q - 1 (and the indices) have been read
+          if (MORE > 1 && q > 0) load_slot(q - 1);
+          wait_loads<(MORE > 1 ? 2 * S::LOADS : 0)>();  // slot q holds step j + 1 (two slots' loads were issued after it)
+          read_slot(q);
         }
-      // the next tile's rows go into this tile's registers as soon as the products have taken
-      // them; their latency is covered by the table writes, the barrier and the wait there for
-      // the waves of the busiest SIMD
-      rows(ix, t1 >= 0 ? t1 : tile, bx, bm);               // tile j + 1 (or a repeat)
-      indices(t2 >= 0 ? t2 : (t1 >= 0 ? t1 : tile), ix);  // tile j + 2 (or a repeat)
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      f32x4_t *tab = red[j & 1];
 #pragma unroll
       for (int nb = 0; nb < NBLK; ++nb) tab[(wv * NBLK + nb) * 64 + lane] = acc[nb];
-      __syncthreads();  // table j % 2 is complete
-      tile = t1;
-      t1 = t2;
-    }
+      wait_lds();
+      if constexpr (MORE > 1) load_slot(KPER - 1);
+      lds_barrier();  // table j % 2 is complete
+      if constexpr (MORE > 1) indices(j + 3);
+    };
+    int j = 0;
+    for (; tile_at(j + 2) >= 0; ++j) step(j, std::integral_constant<int, 2>{});
+    if (tile_at(j + 1) >= 0) step(j++, std::integral_constant<int, 1>{});
+    step(j, std::integral_constant<int, 0>{});
   } else {
-    const int blk0 = wv - KSPLIT, blk1 = blk0 + NRED;  // blk1 < NBLK for wave 9 only
-    for (int j = 0; tile >= 0; ++j) {
-      const int t2 = xcd_tile(blockIdx.x, gridDim.x, ntiles, j + 2);
+    const int rw = wv - KSPLIT, blk1 = rw + NRED;  // blocks rw and, for wave 9, blk1
+    // this reducer's part of a step's indices, straight into the ring: entries rw + 3 u of 64 each
+    // (entries past the 27 offsets repeat the last; rows past the last site take its neighbours:
+    // their results are not stored)
+    auto fetch = [&](int t, int T) {  // of tile t, step T
+      const int r = t * ROWS + (lane & 15), rc = r < n ? r : n - 1;
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        const int g = rw + NRED * u, k = 4 * g + (lane >> 4);
+        if (g < 7) global_to_lds4(nbr + (int64_t)(k < 27 ? k : 26) * cap + rc, lds_address(&ring[T % RING][64 * g]));
+      }
+    };
+#pragma unroll
+    for (int T = 3; T < 6; ++T)
+      if (tile_at(T) >= 0) fetch(tile_at(T), T);
+    float bv[2][4] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+    if (bias)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int blk = rw + NRED * h, o = blk * 16 + 4 * (lane >> 4);
+        if (blk < NBLK && o < cout)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) bv[h][i] = bias[o + i];
+      }
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), known to the compiler (the bias is used in the loop)
+    // step j; `fetching`: there is a step j + 6, whose tile is t6
+    auto step = [&](int j, int tile, int t6, auto fetching) {
       const f32x4_t *tab = red[j & 1];
-      __syncthreads();  // table j % 2 is complete; this wave is done with table (j - 1) % 2
+      // the ring holds step j + 3, which the products read after this barrier: the loads of steps
+      // j + 4 and j + 5 (two or three each) were issued after it
+      wait_loads<(decltype(fetching)::value ? 4 : 0)>();
+      lds_barrier();  // table j % 2 is complete; this wave is done with table (j - 1) % 2
       f32x4_t p0[KSPLIT], p1[KSPLIT];
 #pragma unroll
-      for (int w = 0; w < KSPLIT; ++w) {
-        p0[w] = tab[(w * NBLK + blk0) * 64 + lane];
-        if (blk1 < NBLK) p1[w] = tab[(w * NBLK + blk1) * 64 + lane];
-      }
+      for (int w = 0; w < KSPLIT; ++w) p0[w] = tab[(w * NBLK + rw) * 64 + lane];
+      if (blk1 < NBLK)
+#pragma unroll
+        for (int w = 0; w < KSPLIT; ++w) p1[w] = tab[(w * NBLK + blk1) * 64 + lane];
+      if constexpr (decltype(fetching)::value) fetch(t6, j + 6);  // into the slot last read in step j - 5
+      __builtin_amdgcn_sched_barrier(0);  // all in flight before any is added
       const int r = tile * ROWS + (lane & 15);
       f32x4_t sum = p0[0];
 #pragma unroll
       for (int w = 1; w < KSPLIT; ++w) sum += p0[w];
-      conv_bf16_epilogue_bias(sum, r, n, blk0 * 16 + 4 * (lane >> 4), cout, bv[0], relu, out_f32, Y);
+      conv_bf16_epilogue_bias(sum, r, n, rw * 16 + 4 * (lane >> 4), cout, bv[0], relu, out_f32, Y);
       if (blk1 < NBLK) {
         sum = p1[0];
 #pragma unroll
         for (int w = 1; w < KSPLIT; ++w) sum += p1[w];
         conv_bf16_epilogue_bias(sum, r, n, blk1 * 16 + 4 * (lane >> 4), cout, bv[1], relu, out_f32, Y);
       }
-      tile = t1;
-      t1 = t2;
-    }
+    };
+    int j = 0, t = tile0;
+    for (int t6 = tile_at(6); t6 >= 0; t6 = tile_at(++j + 6), t = tile_at(j)) step(j, t, t6, std::true_type{});
+    for (; t >= 0; t = tile_at(++j)) step(j, t, 0, std::false_type{});
   }
 }
 
@@ -1229,7 +1349,8 @@ npvs_status conv_fwd_dispatch(const void *X, int32_t cin, const void *Wp, const 
     return fail(NPVS_ERR_UNSUPPORTED, "npvs_sparse_conv_fwd: BF16 needs cin % 8 == 0 and cout % 8 == 0");
   const int KB = (cin + 31) / 32, NB = (cout + 15) / 16;
   if (variant == 15) {  // variant 14 with dedicated reducer waves: at most 64 inputs and outputs
-    if (KB <= 2 && NB <= 4) {
+    // (row indices are 24 bits there)
+    if (KB <= 2 && NB <= 4 && cap < (1 << 24)) {
       int G = 256;
       const int most = stride_grid(cap, 16, 4096);
       if (G > most) G = (most + 7) & ~7;

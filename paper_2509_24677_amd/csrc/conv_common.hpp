@@ -59,8 +59,8 @@ __device__ __forceinline__ void conv_bf16_epilogue_bias(const f32x4_t &acc, int 
     *reinterpret_cast<float4 *>(static_cast<float *>(Y) + (int64_t)r * cout + o) = make_float4(v[0], v[1], v[2], v[3]);
   } else {
     uint2 p;
-    p.x = (uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16);
-    p.y = (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16);
+    p.x = f32x2_to_bf16(v[0], v[1]);
+    p.y = f32x2_to_bf16(v[2], v[3]);
     *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(Y) + (int64_t)r * cout + o) = p;
   }
 }
@@ -79,8 +79,8 @@ __device__ __forceinline__ void conv_bf16_epilogue(const f32x4_t &acc, int r, in
     *reinterpret_cast<float4 *>(static_cast<float *>(Y) + (int64_t)r * cout + o) = make_float4(v[0], v[1], v[2], v[3]);
   } else {
     uint2 p;
-    p.x = (uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16);
-    p.y = (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16);
+    p.x = f32x2_to_bf16(v[0], v[1]);
+    p.y = f32x2_to_bf16(v[2], v[3]);
     *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(Y) + (int64_t)r * cout + o) = p;
   }
 }

@@ -199,8 +199,8 @@ __global__ __launch_bounds__(256) void loss_dz_kernel(const float *__restrict__ 
       for (int i = 0; i < 4; ++i) a[i].add(g[i]);
       if (dl) *reinterpret_cast<float4 *>(dl + e) = make_float4(g[0], g[1], g[2], g[3]);
       uint2 h;
-      h.x = (uint32_t)f32_to_bf16(g[0]) | ((uint32_t)f32_to_bf16(g[1]) << 16);
-      h.y = (uint32_t)f32_to_bf16(g[2]) | ((uint32_t)f32_to_bf16(g[3]) << 16);
+      h.x = f32x2_to_bf16(g[0], g[1]);
+      h.y = f32x2_to_bf16(g[2], g[3]);
       *reinterpret_cast<uint2 *>(dZ16 + e) = h;
     }
   }

@@ -189,8 +189,8 @@ __global__ __launch_bounds__(256) void strided_bf16_kernel(const uint16_t *__res
           *reinterpret_cast<f32x4_t *>(static_cast<float *>(Y) + (int64_t)r * cout + o) = f32x4_t{v[0], v[1], v[2], v[3]};
         } else {
           uint2 h;
-          h.x = (uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16);
-          h.y = (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16);
+          h.x = f32x2_to_bf16(v[0], v[1]);
+          h.y = f32x2_to_bf16(v[2], v[3]);
           *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(Y) + (int64_t)r * cout + o) = h;
         }
       }
