@@ -33,11 +33,24 @@ struct Batch {
   GridDesc g[NPVS_MAX_GRIDS];
 };
 
-// Grid of a global block key (linear scan: at most NPVS_MAX_GRIDS grids).
+// Grid of a global block key.  Every lane compares with every grid's first key (at most
+// NPVS_MAX_GRIDS), which are scalar loads at a uniform index: a search that stops early would index
+// the descriptors per lane, one dependent memory round trip a grid.
 __device__ __forceinline__ int grid_of_key(const Batch &B, int32_t key) {
   int b = 0;
-  while (b + 1 < B.n && key >= B.g[b + 1].key_off) ++b;
+  for (int i = 1; i < B.n; ++i) b += key >= B.g[i].key_off ? 1 : 0;
   return b;
+}
+
+// The descriptor of grid b: of one grid for the whole wave where its lanes agree (scalar loads).
+struct BlockGrid {
+  int32_t nx, ny, Bx, By, Bz, key_off;
+  int64_t occ_off;
+};
+__device__ __forceinline__ BlockGrid block_grid(const Batch &B, int b) {
+  const int u = __builtin_amdgcn_readfirstlane(b);
+  const GridDesc &g = B.g[__all(b == u) ? u : b];
+  return BlockGrid{g.nx, g.ny, g.Bx, g.By, g.Bz, g.key_off, g.occ_off};
 }
 
 // ------------------------------------------------------------------------------------------
