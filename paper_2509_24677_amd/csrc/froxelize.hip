@@ -335,25 +335,30 @@ __device__ __forceinline__ uint32_t frox_row(const TriSetup &S, int xa, int xb, 
   return m;
 }
 
-// Culling against a PVS.  A workgroup takes 256 triangles: each thread quantizes one and stages
-// its overlap constants in LDS, a scan of the rows (y, z) each range covers gives a flat list of
-// (triangle, row) items, and each thread tests one row at a time: the PVS word(s) of the row
-// first, the exact overlap test only where a visible froxel lies in the range.  A hit sets the
-// triangle's flag in LDS (a plain store of 1), and rows of flagged triangles are skipped.
+// Culling against a PVS.  A workgroup takes TRIS triangles: each lane of its first wave
+// quantizes one and stages its overlap constants in LDS, a scan of the rows (y, z) each range covers
+// gives a flat list of (triangle, row) items, and each thread tests one row at a time: the PVS
+// word(s) of the row first (one load where the words are aligned), the exact overlap test only where
+// a visible froxel lies in the range.  A hit sets the triangle's flag in LDS (a plain store of 1), and
+// rows of flagged triangles are skipped.
+// Bound by latency: a row is a search of TRIS offsets in LDS, a PVS load and a short test, twelve of
+// them a triangle, and all of a workgroup's triangles are set up by one wave first.  256 triangles a
+// workgroup left most CUs one workgroup or none (50,000 triangles in a city frame: 196, 50.3 us; 13.7
+// now; 200 triangles 19.8 and 6.9 us, 1,000,000 188 and 158 us).
+template <int TRIS>
 __global__ __launch_bounds__(256) void visible_tris_kernel(const float *__restrict__ tris, Batch B, int64_t total,
-                                                            const uint8_t *__restrict__ pvs,
+                                                            const uint8_t *__restrict__ pvs, int words,
                                                             uint8_t *__restrict__ visible) {
-  __shared__ TriSetup srec[256];
-  __shared__ int row0[257];
-  __shared__ int wsum[4];
-  __shared__ int gidx[256];
-  __shared__ uint32_t flag[256];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  for (int64_t base = (int64_t)blockIdx.x * 256; base < total; base += (int64_t)gridDim.x * 256) {
+  __shared__ TriSetup srec[TRIS];
+  __shared__ int row0[TRIS + 1];
+  __shared__ int gidx[TRIS];
+  __shared__ uint32_t flag[TRIS];
+  const int tid = threadIdx.x;
+  for (int64_t base = (int64_t)blockIdx.x * TRIS; base < total; base += (int64_t)gridDim.x * TRIS) {
     const int64_t t = base + tid;
+    const bool mine = tid < TRIS && t < total;
     int rows = 0;
-    flag[tid] = 0;
-    if (t < total) {
+    if (mine) {
       const int b = tri_grid(B, t);
       int32_t q[9], lo[3], hi[3];
       TriSetup S = {};
@@ -368,21 +373,22 @@ __global__ __launch_bounds__(256) void visible_tris_kernel(const float *__restri
       gidx[tid] = b;
       if (!empty) rows = (hi[1] - lo[1] + 1) * (hi[2] - lo[2] + 1);
     }
-    int x = rows;
+    if (tid < 64) {
+      int x = rows;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(x, o, 64);
-      if (lane >= o) x += y;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o, 64);
+        if (tid >= o) x += y;
+      }
+      if (tid < TRIS) {
+        row0[tid] = x - rows;
+        flag[tid] = 0;
+      }
+      if (tid == TRIS - 1) row0[TRIS] = x;
     }
-    if (lane == 63) wsum[w] = x;
-    __syncthreads();  // also orders the previous chunk's reads before these writes
-    int pre = 0;
-    for (int k = 0; k < w; ++k) pre += wsum[k];
-    row0[tid] = pre + x - rows;
-    if (tid == 255) row0[256] = pre + x;
     __syncthreads();
-    const int R = row0[256];
-    const int n = total - base < 256 ? (int)(total - base) : 256;
+    const int R = row0[TRIS];
+    const int n = total - base < TRIS ? (int)(total - base) : TRIS;
     for (int r = tid; r < R; r += 256) {
       int lo = 0, hi = n - 1;  // last staged triangle whose rows start at or before r
       while (lo < hi) {
@@ -399,9 +405,13 @@ __global__ __launch_bounds__(256) void visible_tris_kernel(const float *__restri
       for (int X0 = S.lo[0] & ~31; X0 <= S.hi[0]; X0 += 32) {
         const int xa = S.lo[0] > X0 ? S.lo[0] : X0, xb = S.hi[0] < X0 + 31 ? S.hi[0] : X0 + 31;
         uint32_t m = 0;  // PVS bits of froxels X0 .. X0 + 31 (bytes past the row read as 0)
+        if (words) {
+          m = *reinterpret_cast<const uint32_t *>(row + (X0 >> 3));
+        } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (X0 + 8 * k < g.nx) m |= (uint32_t)row[(X0 >> 3) + k] << (8 * k);
+          for (int k = 0; k < 4; ++k)
+            if (X0 + 8 * k < g.nx) m |= (uint32_t)row[(X0 >> 3) + k] << (8 * k);
+        }
         m &= (xb - X0 == 31 ? ~0u : ((2u << (xb - X0)) - 1u)) & ~((1u << (xa - X0)) - 1u);
         if (m && (frox_row(S, xa, xb, y, z, X0) & m)) {
           flag[lo] = 1u;
@@ -410,7 +420,7 @@ __global__ __launch_bounds__(256) void visible_tris_kernel(const float *__restri
       }
     }
     __syncthreads();
-    if (t < total) visible[t] = flag[tid] ? 1 : 0;
+    if (mine) visible[t] = flag[tid] ? 1 : 0;
     __syncthreads();  // flags and staging are rewritten by the next chunk
   }
 }
@@ -695,8 +705,24 @@ extern "C" npvs_status npvs_visible_triangles(const float *tris, const int64_t *
   for (int b = 0; b < n_grids; ++b) total += n_tris[b];
   if (total == 0) return NPVS_OK;
   if (!tris || !visible) return fail(NPVS_ERR_INVALID_ARG, "npvs_visible_triangles: null triangles or output");
-  visible_tris_kernel<<<stride_grid(total, 256, 4096), 256, 0, as_stream(stream)>>>(tris, B, total, pvs_bits,
-                                                                                      visible);
+  // whole aligned PVS words: every x extent a multiple of 32 and an aligned grid
+  bool words = (reinterpret_cast<uintptr_t>(pvs_bits) & 3) == 0;
+  for (int b = 0; b < n_grids; ++b) words = words && dims[b].nx % 32 == 0;
+  // Triangles a workgroup: few while workgroups are few, more as setup and staging count.  Measured in
+  // city scenes (us, 16 / 32 / 48 / 64 a workgroup): 8,000 triangles 8.7 / 9.6 / 12.0 / 13.6; 20,000
+  // 12.9 / 9.9 / 12.4 / 14.7; 50,000 21.4 / 15.8 / 13.7 / 15.7; 200,000 68 / 44 / 37.4 / 38.2; 1,000,000
+  // 340 / 211 / 171 / 158.
+  auto launch = [&](auto kernel, int tris_per_wg) {
+    kernel<<<stride_grid(total, tris_per_wg, 8192), 256, 0, as_stream(stream)>>>(tris, B, total, pvs_bits, words, visible);
+  };
+  if (total <= 10000)
+    launch(visible_tris_kernel<16>, 16);
+  else if (total <= 32768)
+    launch(visible_tris_kernel<32>, 32);
+  else if (total <= 300000)
+    launch(visible_tris_kernel<48>, 48);
+  else
+    launch(visible_tris_kernel<64>, 64);
   return check_hip(hipGetLastError(), "npvs_visible_triangles");
 }
 
