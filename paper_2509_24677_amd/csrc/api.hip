@@ -1,6 +1,7 @@
 // Host side of the C ABI: argument checking, error text, batch descriptors, and the plan that
 // runs the whole forward pass (froxelize -> sites/rulebook -> interleave -> convolutions ->
 // de-interleave + threshold) on one stream, optionally captured into a HIP graph.
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -29,6 +30,9 @@ npvs_status make_batch(int32_t n_grids, const npvs_dims *dims, int32_t d, const 
   if (n_grids < 1 || n_grids > NPVS_MAX_GRIDS) return fail(NPVS_ERR_INVALID_ARG, "n_grids must be in [1, 32]");
   if (d < 1 || d > 32 || (d & (d - 1))) return fail(NPVS_ERR_INVALID_ARG, "d must be a power of two in [1, 32]");
   std::memset(B, 0, sizeof(*B));
+  std::fill_n(B->key0, NPVS_MAX_GRIDS, INT32_MAX);
+  std::fill_n(B->tile0, NPVS_MAX_GRIDS, INT32_MAX);
+  std::fill_n(B->tri0, NPVS_MAX_GRIDS, INT64_MAX);
   B->n = n_grids;
   B->d = d;
   int64_t key = 0, tile = 0, occ = 0, dense = 0, tri = 0;
@@ -53,6 +57,9 @@ npvs_status make_batch(int32_t n_grids, const npvs_dims *dims, int32_t d, const 
     G.tiles_y = (g.ny + kFroxTileY - 1) / kFroxTileY;
     G.tiles_z = (g.nz + kFroxTileZ - 1) / kFroxTileZ;
     G.tri_off = tri;
+    B->key0[b] = G.key_off;
+    B->tile0[b] = G.tile_off;
+    B->tri0[b] = tri;
     G.tri_n = 0;
     if (n_tris) {
       if (n_tris[b] < 0 || n_tris[b] > INT32_MAX) return fail(NPVS_ERR_INVALID_ARG, "bad triangle count");

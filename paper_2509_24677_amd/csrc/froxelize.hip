@@ -39,7 +39,8 @@ struct TriSetup {
   int32_t H[3][3];
   int16_t lo[3], hi[3];  // clipped froxel range; lo > hi when empty or ignored
 };
-static_assert(sizeof(TriSetup) % 16 == 0, "setup record is loaded as 16-byte words");
+static_assert(sizeof(TriSetup) % 16 == 0, "setup record is stored as 16-byte words");
+constexpr int kRecWords = sizeof(TriSetup) / 16;
 
 constexpr int kTileWords = (kFroxTileX / 32) * kFroxTileY * kFroxTileZ;  // 64
 constexpr int kPartTris = 64;  // triangles of a chunk of the parts path
@@ -54,28 +55,14 @@ __global__ void frox_zero_kernel(int32_t *p, int n, int32_t *n_ignored, uint32_t
 }
 
 __device__ __forceinline__ int tri_grid(const Batch &B, int64_t t) {
-  int b = 0;
-  while (b + 1 < B.n && t >= B.g[b + 1].tri_off) ++b;
-  return b;
+  return grid_search(B.tri0, B.n, t);
 }
 
 // L = ceil((min_v a.q_v - 256 sum_c max(0, a_c)) / 256), H = floor((max_v a.q_v - 256 sum_c min(0, a_c)) / 256):
 // the box [256 I, 256 I + 256] projects onto [256 a.I + R-, 256 a.I + R+].  A zero axis gives
-// L = H = 0 = a . I and never separates.
-__device__ __forceinline__ void axis_bounds(int64_t a0, int64_t a1, int64_t a2, const int32_t *q, int64_t &L,
-                                            int64_t &H) {
-  int64_t p0 = a0 * q[0] + a1 * q[1] + a2 * q[2];
-  int64_t p1 = a0 * q[3] + a1 * q[4] + a2 * q[5];
-  int64_t p2 = a0 * q[6] + a1 * q[7] + a2 * q[8];
-  int64_t pmin = p0 < p1 ? p0 : p1, pmax = p0 > p1 ? p0 : p1;
-  pmin = p2 < pmin ? p2 : pmin;
-  pmax = p2 > pmax ? p2 : pmax;
-  int64_t rp = 256 * ((a0 > 0 ? a0 : 0) + (a1 > 0 ? a1 : 0) + (a2 > 0 ? a2 : 0));
-  int64_t rm = 256 * ((a0 < 0 ? a0 : 0) + (a1 < 0 ? a1 : 0) + (a2 < 0 ? a2 : 0));
-  L = (pmin - rp + 255) >> 8;  // ceil division by 256 (arithmetic shift floors)
-  H = (pmax - rm) >> 8;
-}
-
+// L = H = 0 = a . I and never separates.  An axis at right angles to an edge sees the edge's two
+// vertices at one place, so e_i x box axis has two projections to compare (of vertices i and i + 2)
+// and the normal a single one; an edge axis has two components, each product 32 x 32 bits.
 __device__ __forceinline__ int32_t clamp_i32(int64_t v) {
   return v < (int64_t)INT32_MIN ? INT32_MIN : v > (int64_t)INT32_MAX ? INT32_MAX : (int32_t)v;
 }
@@ -92,20 +79,25 @@ __device__ __forceinline__ void make_setup(const int32_t *q, TriSetup &S) {
   S.n[0] = (int64_t)e[0][1] * e[1][2] - (int64_t)e[0][2] * e[1][1];
   S.n[1] = (int64_t)e[0][2] * e[1][0] - (int64_t)e[0][0] * e[1][2];
   S.n[2] = (int64_t)e[0][0] * e[1][1] - (int64_t)e[0][1] * e[1][0];
-  axis_bounds(S.n[0], S.n[1], S.n[2], q, S.nL, S.nH);
-  int64_t L, H;
+  const int64_t p = S.n[0] * q[0] + S.n[1] * q[1] + S.n[2] * q[2];
+  int64_t rp = 0, rm = 0;
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    axis_bounds(0, e[i][2], -e[i][1], q, L, H);
-    S.L[i][0] = clamp_i32(L);
-    S.H[i][0] = clamp_i32(H);
-    axis_bounds(-e[i][2], 0, e[i][0], q, L, H);
-    S.L[i][1] = clamp_i32(L);
-    S.H[i][1] = clamp_i32(H);
-    axis_bounds(e[i][1], -e[i][0], 0, q, L, H);
-    S.L[i][2] = clamp_i32(L);
-    S.H[i][2] = clamp_i32(H);
-  }
+  for (int c = 0; c < 3; ++c) (S.n[c] > 0 ? rp : rm) += S.n[c];
+  S.nL = (p - 256 * rp + 255) >> 8;  // ceil division by 256 (arithmetic shift floors)
+  S.nH = (p - 256 * rm) >> 8;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {  // e_i x axis a = (.., a1 at c1, a2 at c2)
+      const int c1 = (a + 1) % 3, c2 = (a + 2) % 3, k = (i + 2) % 3;
+      const int32_t a1 = e[i][c2], a2 = -e[i][c1];
+      const int64_t p0 = (int64_t)a1 * q[i * 3 + c1] + (int64_t)a2 * q[i * 3 + c2];
+      const int64_t p1 = (int64_t)a1 * q[k * 3 + c1] + (int64_t)a2 * q[k * 3 + c2];
+      const int32_t r1 = 256 * ((a1 > 0 ? a1 : 0) + (a2 > 0 ? a2 : 0));  // below 2^29
+      const int32_t r0 = 256 * ((a1 < 0 ? a1 : 0) + (a2 < 0 ? a2 : 0));
+      S.L[i][a] = clamp_i32(((p0 < p1 ? p0 : p1) - r1 + 255) >> 8);
+      S.H[i][a] = clamp_i32(((p0 > p1 ? p0 : p1) - r0) >> 8);
+    }
 }
 
 // Fixed-point vertices (rint(256 v), round half to even) and the clipped closed-froxel range of
@@ -147,7 +139,13 @@ __device__ __forceinline__ bool quantize_tri(const float *__restrict__ tris, int
 }
 
 // LDS table of the tiles one workgroup appends to (open addressing on the tile index).
-constexpr int kBinSlots = 512;
+// Twice the tiles that 256 scattered triangles meet: with 512 entries, nearly full, searches of
+// hundreds of entries held one workgroup of a batch for 20,000 cycles (6,000 now).
+constexpr int kBinSlots = 1024;
+constexpr int kBinProbes = 16;
+// Tile counters lie 16 bytes apart: updates that share a line come one after the other (a city frame's
+// wait for them 12,500 -> 9,700 cycles).
+constexpr int kCountStride = 4;
 constexpr int kBinKeep = 8;  // (triangle, tile) appends a thread remembers; more go straight to memory
 
 // Chunk list entries: tile * 64 + c, c < kListedChunks a chunk of 64 listed triangles, c >=
@@ -172,6 +170,11 @@ __device__ __forceinline__ void write_chunks(int tile, int base, int k, int32_t 
     for (int c = 0; c < kListedChunks; ++c) chunks[pos++] = tile * kChunkCodes + kListedChunks + c;
 }
 
+// Bound by its chain of round trips: triangle, table, tile counter, chunk count, lists.  16-byte record
+// stores by whole lines at the end (a lane's own record store touched ten lines, and the counters'
+// answers waited behind them), 32 x 32-bit products and no third projection in the setup, the packed
+// grid search and the wider table took a city frame's 50,000 triangles from 19.3 to 15.8 us and sixteen
+// uneven grids' 16,000 from 18.4 to 13.2.
 __global__ __launch_bounds__(256) void frox_bin_kernel(const float *__restrict__ tris, Batch B, int64_t total,
                                                         TriSetup *__restrict__ recs, int32_t *__restrict__ tile_count,
                                                         int32_t *__restrict__ tile_list, int32_t *__restrict__ n_ignored,
@@ -179,6 +182,8 @@ __global__ __launch_bounds__(256) void frox_bin_kernel(const float *__restrict__
   __shared__ int htile[kBinSlots];
   __shared__ int hcount[kBinSlots];
   __shared__ int hbase[kBinSlots];
+  __shared__ int kept[kBinKeep][256];  // table entry and slot << 16 of a thread's appends; < 0: none
+  __shared__ __align__(16) TriSetup srec[256];
   for (int i = threadIdx.x; i < kBinSlots; i += blockDim.x) {
     htile[i] = -1;
     hcount[i] = 0;
@@ -197,7 +202,7 @@ __global__ __launch_bounds__(256) void frox_bin_kernel(const float *__restrict__
       S.lo[a] = (int16_t)(empty ? 1 : lo[a]);
       S.hi[a] = (int16_t)(empty ? 0 : hi[a]);
     }
-    recs[t] = S;
+    srec[threadIdx.x] = S;
     if (!empty) {
       tx0 = lo[0] / kFroxTileX;
       ty0 = lo[1] / kFroxTileY;
@@ -220,54 +225,62 @@ __global__ __launch_bounds__(256) void frox_bin_kernel(const float *__restrict__
   // the entry's range.  Consecutive triangles mostly share tiles, so a tile that hundreds of
   // triangles meet sees a few global updates instead of hundreds.  An append that finds no free
   // table entry, or a thread's appends past kBinKeep, take a global slot directly.
-  auto tile_of = [&](int j) {
-    const int ix = j % ntx, iy = (j / ntx) % nty, iz = j / (ntx * nty);
-    return toff + ((tz0 + iz) * tys + (ty0 + iy)) * txs + (tx0 + ix);
+  int ix = 0, iy = 0, iz = 0;  // the tile of the range that the walk below stands at
+  auto tile_here = [&] { return toff + ((tz0 + iz) * tys + (ty0 + iy)) * txs + (tx0 + ix); };
+  auto step = [&] {
+    if (++ix == ntx) {
+      ix = 0;
+      if (++iy == nty) {
+        iy = 0;
+        ++iz;
+      }
+    }
   };
   auto append = [&](int tile, int slot) {
     if (slot < kFroxTileCap) tile_list[(int64_t)tile * kFroxTileCap + slot] = (int32_t)t;
   };
   // an append that reserved its slot alone lists the chunks it starts itself
   auto direct = [&](int tile) {
-    const int slot = atomicAdd(&tile_count[tile], 1);
+    const int slot = atomicAdd(&tile_count[tile * kCountStride], 1);
     append(tile, slot);
     if (chunks) {
       const int k = chunks_started(slot, 1);
       if (k) write_chunks(tile, slot, 1, chunks, atomicAdd(n_chunks, k));
     }
   };
-  int kslot[kBinKeep], kent[kBinKeep];
-#pragma unroll
-  for (int j = 0; j < kBinKeep; ++j) {
-    kent[j] = -1;
-    kslot[j] = 0;
-    if (j < ntl) {
-      const int tile = tile_of(j);
-      int h = (int)(((uint32_t)tile * 2654435761u) >> 23) & (kBinSlots - 1);
-      for (int probe = 0; probe < kBinSlots; ++probe, h = (h + 1) & (kBinSlots - 1)) {
-        const int cur = atomicCAS(&htile[h], -1, tile);
-        if (cur == -1 || cur == tile) {
-          kent[j] = h;
-          kslot[j] = atomicAdd(&hcount[h], 1);
-          break;
-        }
+  for (int j = 0; j < kBinKeep && j < ntl; ++j, step()) {
+    const int tile = tile_here();
+    int h = (int)(((uint32_t)tile * 2654435761u) >> 22) & (kBinSlots - 1), v = -1;
+    for (int probe = 0; probe < kBinProbes; ++probe, h = (h + 1) & (kBinSlots - 1)) {
+      // a plain read first: lanes share it, where exchanges of one word come one lane at a time
+      int cur = *(volatile int *)&htile[h];
+      if (cur == -1) cur = atomicCAS(&htile[h], -1, tile);
+      if (cur == -1 || cur == tile) {
+        v = h | atomicAdd(&hcount[h], 1) << 16;
+        break;
       }
-      if (kent[j] < 0) direct(tile);  // table full
     }
+    kept[j][threadIdx.x] = v;
+    if (v < 0) direct(tile);
   }
-  for (int j = kBinKeep; j < ntl; ++j) direct(tile_of(j));  // large triangles: the rest directly
+  for (int j = kBinKeep; j < ntl; ++j, step()) direct(tile_here());  // large triangles: the rest directly
   __syncthreads();
   // one counter update per table entry, then the chunks the workgroup's ranges start: one update
   // of the chunk count for the whole workgroup
   __shared__ int wsum[4];
   __shared__ int cbase;
-  int nch[kBinSlots / 256] = {};
+  int nch[kBinSlots / 256] = {}, first[kBinSlots / 256];
+#pragma unroll
+  for (int u = 0; u < kBinSlots / 256; ++u) {  // all updates in flight before the first answer
+    const int i = threadIdx.x + 256 * u;
+    if (htile[i] >= 0) first[u] = atomicAdd(&tile_count[htile[i] * kCountStride], hcount[i]);
+  }
 #pragma unroll
   for (int u = 0; u < kBinSlots / 256; ++u) {
     const int i = threadIdx.x + 256 * u;
     if (htile[i] >= 0) {
-      hbase[i] = atomicAdd(&tile_count[htile[i]], hcount[i]);
-      if (chunks) nch[u] = chunks_started(hbase[i], hcount[i]);
+      hbase[i] = first[u];
+      if (chunks) nch[u] = chunks_started(first[u], hcount[i]);
     }
   }
   if (chunks) {
@@ -301,9 +314,15 @@ __global__ __launch_bounds__(256) void frox_bin_kernel(const float *__restrict__
     }
   }
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < kBinKeep; ++j)
-    if (kent[j] >= 0) append(htile[kent[j]], hbase[kent[j]] + kslot[j]);
+  for (int j = 0; j < kBinKeep && j < ntl; ++j) {
+    const int v = kept[j][threadIdx.x], ent = v & (kBinSlots - 1);
+    if (v >= 0) append(htile[ent], hbase[ent] + (v >> 16));
+  }
+  // the records last and in whole lines (written when the counters' barriers had passed)
+  const int64_t t0 = (int64_t)blockIdx.x * 256;
+  const int words = (int)(total - t0 < 256 ? total - t0 : 256) * kRecWords;
+  for (int i = threadIdx.x; i < words; i += 256)
+    reinterpret_cast<int4 *>(recs + t0)[i] = reinterpret_cast<const int4 *>(srec)[i];
 }
 
 // Froxels x in [xa, xb] of row (y, z) that the triangle meets, as bits x - X0 of a 32-bit word.
@@ -343,8 +362,8 @@ __device__ __forceinline__ uint32_t frox_row(const TriSetup &S, int xa, int xb, 
 // rows of flagged triangles are skipped.
 // Bound by latency: a row is a search of TRIS offsets in LDS, a PVS load and a short test, twelve of
 // them a triangle, and all of a workgroup's triangles are set up by one wave first.  256 triangles a
-// workgroup left most CUs one workgroup or none (50,000 triangles in a city frame: 196, 50.3 us; 13.7
-// now; 200 triangles 19.8 and 6.9 us, 1,000,000 188 and 158 us).
+// workgroup left most CUs one workgroup or none (50,000 triangles in a city frame: 196, 50.3 us; 13.3
+// now; 200 triangles 19.8 and 6.5 us, 1,000,000 188 and 117 us).
 template <int TRIS>
 __global__ __launch_bounds__(256) void visible_tris_kernel(const float *__restrict__ tris, Batch B, int64_t total,
                                                             const uint8_t *__restrict__ pvs, int words,
@@ -437,9 +456,7 @@ __global__ __launch_bounds__(256) void visible_objects_kernel(const uint8_t *__r
 }
 
 __device__ __forceinline__ const GridDesc &tile_grid(const Batch &B, int tile) {
-  int b = 0;
-  while (b + 1 < B.n && tile >= B.g[b + 1].tile_off) ++b;
-  return B.g[b];
+  return B.g[grid_search(B.tile0, B.n, tile)];
 }
 
 __device__ __forceinline__ void tile_origin(const GridDesc &g, int tile, int &X0, int &Y0, int &Z0) {
@@ -472,7 +489,7 @@ __global__ __launch_bounds__(256) void frox_part_kernel(Batch B, const TriSetup 
   for (int ci = blockIdx.x; ci < nc; ci += gridDim.x) {
     const int code = chunks[ci];
     const int tile = code / kChunkCodes, c = code % kChunkCodes;
-    const int cnt = tile_count[tile];
+    const int cnt = tile_count[tile * kCountStride];
     const GridDesc &g = tile_grid(B, tile);
     const bool listed = cnt <= kFroxTileCap;
     if (listed != (c < kListedChunks)) continue;  // uniform: an overflowed tile's listed chunk
@@ -557,7 +574,7 @@ __global__ __launch_bounds__(256) void frox_tile_kernel(Batch B, const TriSetup 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int tile = blockIdx.x;
   const GridDesc &g = tile_grid(B, tile);
-  const int cnt = tile_count[tile];
+  const int cnt = tile_count[tile * kCountStride];
   const bool listed = cnt <= kFroxTileCap;
   const int items = listed ? cnt : g.tri_n;
   int X0, Y0, Z0;
@@ -627,7 +644,7 @@ static void frox_ws_layout(const Batch &B, int64_t total_tris, size_t *off_count
                            size_t *off_recs, size_t *bytes) {
   size_t o = 0;
   *off_count = o;  // tile counters, the chunk count, the chunk list
-  o += align256(sizeof(int32_t) * ((size_t)B.total_tiles + 1 + (size_t)B.total_tiles * kChunkCodes));
+  o += align256(sizeof(int32_t) * ((size_t)B.total_tiles * kCountStride + 1 + (size_t)B.total_tiles * kChunkCodes));
   *off_list = o;
   o += align256(sizeof(int32_t) * (size_t)B.total_tiles * kFroxTileCap);
   *off_recs = o;
@@ -679,9 +696,9 @@ extern "C" npvs_status npvs_froxelize(const float *tris, const int64_t *n_tris, 
     total_bytes += (int64_t)dims[b].nz * dims[b].ny * (dims[b].nx / 8);
   }
   const int64_t n_words = parts ? total_bytes / 4 : 0;
-  int32_t *n_chunks = cnt + B.total_tiles, *chunks = n_chunks + 1;
-  frox_zero_kernel<<<stride_grid(std::max<int64_t>(B.total_tiles + 1, n_words), 256, 1024), 256, 0, s>>>(
-      cnt, B.total_tiles + 1, n_ignored, reinterpret_cast<uint32_t *>(occ_bits), n_words);
+  int32_t *n_chunks = cnt + B.total_tiles * kCountStride, *chunks = n_chunks + 1;
+  frox_zero_kernel<<<stride_grid(std::max<int64_t>(B.total_tiles * kCountStride + 1, n_words), 256, 1024), 256, 0, s>>>(
+      cnt, B.total_tiles * kCountStride + 1, n_ignored, reinterpret_cast<uint32_t *>(occ_bits), n_words);
   if (total > 0)
     frox_bin_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(tris, B, total, recs, cnt, lst, n_ignored,
                                                                      parts ? n_chunks : nullptr,

@@ -165,7 +165,7 @@ __global__ __launch_bounds__(256) void gather_bits_kernel(Batch B, const uint8_t
     int oy = t % d, oz = (t / d) % d;
     int32_t r = (int32_t)(t / ((int64_t)d * d));
     int32_t key = site_keys[r];
-    const GridDesc &g = B.g[grid_of_key(B, key)];
+    const BlockGrid g = block_grid(B, grid_of_key(B, key));
     int32_t l = key - g.key_off;
     int bx = l % g.Bx, by = (l / g.Bx) % g.By, bz = l / (g.Bx * g.By);
     const int64_t row_off = g.occ_off + ((int64_t)(bz * d + oz) * g.ny + (by * d + oy)) * (g.nx >> 3);

@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void sites_count_kernel(Batch B, const uint8_t
 // vec: the table is 16-byte aligned and a thread's blocks are a multiple of four (of one grid), so
 // they are stored four at a time (a store whose lanes lie 4 bpt bytes apart costs a line per lane).
 // Sixteen uneven grids (778,000 blocks at d = 4): 19.6 us block by block with a grid search each, 10.7
-// so; a city frame (131,072 blocks) 7.6 and 5.3.
+// so, 6.9 with the packed grid search; a city frame (131,072 blocks) 7.6 and 5.3.
 __global__ __launch_bounds__(256) void sites_write_kernel(Batch B, const uint8_t *__restrict__ occ, int bpt, int fast,
                                                            int vec, const int32_t *__restrict__ wg_counts, int32_t cap,
                                                            npvs_counts *__restrict__ counts,
@@ -170,7 +170,7 @@ constexpr int kNbrRows = 256;        // rows per workgroup of the neighbour kern
 // are added to the (zeroed) counts of the 1024-row chunks.  Bound by the latency of the chain count,
 // key, descriptor, probes.  With a thread per (row, offset) that chain, the three divisions and a
 // serial grid search came 27 times a row: 9.1 us for a city frame, 20.0 for sixteen uneven grids; now
-// 5.0 and 9.5.
+// 5.0 and 6.3.
 __global__ __launch_bounds__(256) void rulebook_nbr_kernel(Batch B, const int32_t *__restrict__ site_keys,
                                                             const int32_t *__restrict__ block_row,
                                                             const npvs_counts *__restrict__ counts, int32_t cap,
