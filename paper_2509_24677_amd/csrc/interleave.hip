@@ -253,6 +253,44 @@ __global__ __launch_bounds__(256) void deinterleave_threshold_kernel(Batch B, in
   }
 }
 
+// The same with dense logits for d >= 4 and rows of 16-byte words: one thread per four froxels, two
+// neighbouring lanes per packed byte, so that a wave stores 1 KB of logits in one piece (a thread with
+// eight froxels stores two 16-byte words 32 bytes apart).  Bound by the logits' store (a plain fill of
+// their 33.6 MB takes 5.7 us for a city frame): 13.2 us by bytes, 12.3 so, 10.9 with the store past the
+// caches, which the logits of a frame do not fit.  Two or four items a thread: 11.8 and 12.1.
+__global__ __launch_bounds__(256) void deinterleave_logits_kernel(Batch B, int64_t total_bytes,
+                                                                   const float *__restrict__ Y, int C,
+                                                                   const int32_t *__restrict__ block_row,
+                                                                   const uint8_t *__restrict__ occ,
+                                                                   uint8_t *__restrict__ pvs,
+                                                                   float *__restrict__ logits) {
+  typedef float F4 __attribute__((ext_vector_type(4)));
+  const int d = B.d, ld = __builtin_ctz(d);
+  const float ninf = -__builtin_huge_valf();
+  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < 2 * total_bytes;
+       u += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t t = u >> 1;
+    const int half = (int)u & 1;
+    int b = 0;
+    while (b + 1 < B.n && t >= B.g[b + 1].occ_off) ++b;
+    const GridDesc &g = B.g[b];
+    // 32-bit index arithmetic: a grid holds at most 1024^3 / 8 bytes
+    const uint32_t l = (uint32_t)(t - g.occ_off), rb = (uint32_t)g.nx >> 3, ny = (uint32_t)g.ny;
+    const uint32_t ly = l / rb;
+    const int x = (int)(l - ly * rb) * 8 + 4 * half, z = (int)(ly / ny), y = (int)(ly - (uint32_t)z * ny);
+    const int32_t row = block_row[g.key_off + ((z >> ld) * g.By + (y >> ld)) * g.Bx + (x >> ld)];
+    const int c = ((((z & (d - 1)) << ld) + (y & (d - 1))) << ld) + (x & (d - 1));
+    const uint32_t gbits = occ[t];
+    const F4 v = row >= 0 ? *reinterpret_cast<const F4 *>(Y + (int64_t)row * C + c) : F4{ninf, ninf, ninf, ninf};
+    __builtin_nontemporal_store(
+        v, reinterpret_cast<F4 *>(logits + g.dense_off + (((int64_t)z * g.ny + y) * g.nx + x)));
+    const uint32_t m = (uint32_t)(v.x >= 0.0f) | (uint32_t)(v.y >= 0.0f) << 1 | (uint32_t)(v.z >= 0.0f) << 2 |
+                       (uint32_t)(v.w >= 0.0f) << 3;
+    const uint32_t hi = __shfl_down(m, 1, 64);  // both lanes of a byte are here: 2 total_bytes is even
+    if (half == 0) pvs[t] = (uint8_t)((m | hi << 4) & gbits);
+  }
+}
+
 }  // namespace npvs
 
 using namespace npvs;
@@ -328,6 +366,11 @@ extern "C" npvs_status npvs_deinterleave_threshold(const float *Y, int32_t y_str
   for (int b = 0; b < n_grids; ++b) total += (int64_t)dims[b].nz * dims[b].ny * (dims[b].nx / 8);
   const int C = d * d * d, stride = y_stride ? y_stride : C;
   if (stride < C) return fail(NPVS_ERR_INVALID_ARG, "npvs_deinterleave_threshold: y_stride below d^3");
+  if (logits && d >= 4 && stride % 4 == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0) {
+    deinterleave_logits_kernel<<<stride_grid(2 * total, 256, 8192), 256, 0, as_stream(stream)>>>(
+        B, total, Y, stride, block_row, occ_bits, pvs_bits, logits);
+    return check_hip(hipGetLastError(), "npvs_deinterleave_threshold");
+  }
   int grid = stride_grid(total, 256, 8192);
   deinterleave_threshold_kernel<<<grid, 256, 0, as_stream(stream)>>>(B, total, Y, stride, block_row, occ_bits,
                                                                       pvs_bits, logits);
