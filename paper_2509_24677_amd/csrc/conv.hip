@@ -464,35 +464,32 @@ __global__ __launch_bounds__(64 * KSPLIT) void conv_fwd_bf16_kernel(const uint16
 // BF16 path for any channel counts (cin % 8 == 0, cout % 8 == 0), used for the shapes the tuned
 // kernels above do not cover, e.g. the wide first and last layers of interleave factors 8 and 16
 // (Cin or Cout = d^3 = 512 or 4096).  Workgroup = 9 waves over the same MB x 16 rows, wave w owning
-// offsets 3w .. 3w + 2; blockIdx.y selects 64 output channels (4 MFMA output blocks).  The
+// offsets 3w .. 3w + 2; blockIdx.z selects 64 output channels (4 MFMA output blocks).  The
 // (offset, 32-channel chunk) stages are walked with a runtime chunk count and 4 stages in flight;
 // loads past the last stage re-read it and are masked to zero, and offsets with no neighbour
 // gather zeros, so every MFMA is unconditional (no branch around an accumulator).  The 9 partial
 // sums are added in LDS in wave order, as in the split kernel.
 // ------------------------------------------------------------------------------------------
 template <int MB>
-__global__ __launch_bounds__(576) void conv_fwd_bf16_wide_kernel(const uint16_t *__restrict__ X, int cin,
-                                                                  const bf16x8_t *__restrict__ Wp,
-                                                                  const float *__restrict__ bias, int cout,
-                                                                  const int32_t *__restrict__ nbr,
-                                                                  const npvs_counts *__restrict__ counts, int cap,
-                                                                  int relu, int out_f32, void *__restrict__ Y,
-                                                                  float *__restrict__ part) {
-  constexpr int KSPLIT = 9, KPER = 3, ROWS = 16 * MB, NBLK = MB * 4, PD = 4;
-  __shared__ f32x4_t red[KSPLIT * NBLK * 64];
-  const int32_t n = counts->n_sites;
+__device__ __forceinline__ void conv_bf16_wide_body(const uint16_t *__restrict__ X, int cin,
+                                                    const bf16x8_t *__restrict__ Wp, const float *__restrict__ bias,
+                                                    int cout, const int32_t *__restrict__ nbr, int n, int cap, int relu,
+                                                    int out_f32, void *__restrict__ Y, float *__restrict__ part,
+                                                    f32x4_t *__restrict__ red) {
+  constexpr int KSPLIT = 9, KPER = 3, ROWS = 16 * MB, NBLK = MB * 4, PD = MB > 2 ? 2 : 4;
   const int ntiles = (n + ROWS - 1) / ROWS;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, uniform (scalar)
   const int kbeg = wv * KPER, csub = 8 * (lane >> 4);
-  const int KB = (cin + 31) / 32, NBT = (cout + 15) / 16, nb0 = 4 * blockIdx.y;
-  // input-channel split (gridDim.z > 1 only with `part`): this workgroup's 32-channel chunks
-  const int KBZ = (KB + gridDim.z - 1) / gridDim.z, kb_lo = blockIdx.z * KBZ;
+  const int KB = (cin + 31) / 32, NBT = (cout + 15) / 16, nb0 = 4 * blockIdx.z;
+  // input-channel split (gridDim.x > 1 only with `part`): this workgroup's 32-channel chunks
+  const int KBZ = (KB + gridDim.x - 1) / gridDim.x, kb_lo = blockIdx.x * KBZ;
   const int nkb = KB - kb_lo < KBZ ? KB - kb_lo : KBZ;
   const int S = KPER * nkb;  // stages of this wave
   for (int j = 0;; ++j) {
-    const int tile = xcd_tile(blockIdx.x, gridDim.x, ntiles, j);
-    if (tile < 0) break;
+    int tile = blockIdx.y + j * gridDim.y;
+    if (gridDim.x == 1) tile = xcd_tile(blockIdx.y, gridDim.y, ntiles, j);
+    if (tile < 0 || tile >= ntiles) break;
     const int row0 = tile * ROWS;
     const bf16x8_t *W = Wp + opaque_zero();
     int idx[KPER][MB];
@@ -547,11 +544,43 @@ __global__ __launch_bounds__(576) void conv_fwd_bf16_wide_kernel(const uint16_t 
       const int mb = blk / 4, nb = blk % 4;
       const int r = row0 + mb * 16 + (lane & 15), o = (nb0 + nb) * 16 + 4 * (lane >> 4);
       if (part) {  // raw partial sum of this channel range; the finishing kernel adds the ranges
-        if (r < n && o < cout) *reinterpret_cast<f32x4_t *>(part + ((int64_t)blockIdx.z * cap + r) * cout + o) = sum;
+        if (r < n && o < cout) *reinterpret_cast<f32x4_t *>(part + ((int64_t)blockIdx.x * cap + r) * cout + o) = sum;
       } else {
         conv_bf16_epilogue<4>(sum, r, n, o, cout, bias, relu, out_f32, Y);
       }
     }
+  }
+}
+
+// MB = 1, 2 or 4 blocks of 16 rows per workgroup (equal sums either way); 0: by the number of sites.
+// A workgroup reads all its weights once per tile, so more rows a tile read them less often, but fewer
+// tiles leave CUs idle.  A round of 256 workgroups measured 20, 31 and 41 us for MB = 1, 2 and 4 (4096 ->
+// 64 in 16 ranges), hence the least of 2, 3 and 4 times the rounds.  The range is blockIdx.x, so that
+// ranges go to XCDs in turn and an XCD's L2 holds the weights of its own two of 16 (14 MB in all; 40
+// sites 47.2 us with a range's tiles over all XCDs, 22.9 so).  One block a tile before and this, 4096 -> 64, us: 397 sites
+// 50.8 -> 32.3, 1,024 88.8 -> 48.4, 2,048 162.5 -> 92.5; 1024 -> 128, 1,802 sites 85.2 -> 46.8.
+template <int MB>
+__global__ __launch_bounds__(576) void conv_fwd_bf16_wide_kernel(const uint16_t *__restrict__ X, int cin,
+                                                                  const bf16x8_t *__restrict__ Wp,
+                                                                  const float *__restrict__ bias, int cout,
+                                                                  const int32_t *__restrict__ nbr,
+                                                                  const npvs_counts *__restrict__ counts, int cap,
+                                                                  int relu, int out_f32, void *__restrict__ Y,
+                                                                  float *__restrict__ part) {
+  __shared__ f32x4_t red[9 * (MB ? MB : 4) * 4 * 64];
+  const int32_t n = counts->n_sites;
+  if constexpr (MB > 0) {
+    conv_bf16_wide_body<MB>(X, cin, Wp, bias, cout, nbr, n, cap, relu, out_f32, Y, part, red);
+  } else {
+    const int split = gridDim.x * gridDim.z, t = (n + 15) / 16;
+    const int c1 = 2 * ((t * split + 255) / 256), c2 = 3 * (((t + 1) / 2 * split + 255) / 256),
+              c4 = 4 * (((t + 3) / 4 * split + 255) / 256);
+    if (c1 <= c2 && c1 <= c4)
+      conv_bf16_wide_body<1>(X, cin, Wp, bias, cout, nbr, n, cap, relu, out_f32, Y, part, red);
+    else if (c2 <= c4)
+      conv_bf16_wide_body<2>(X, cin, Wp, bias, cout, nbr, n, cap, relu, out_f32, Y, part, red);
+    else
+      conv_bf16_wide_body<4>(X, cin, Wp, bias, cout, nbr, n, cap, relu, out_f32, Y, part, red);
   }
 }
 
@@ -565,6 +594,7 @@ __global__ __launch_bounds__(256) void conv_splitk_finish_kernel(const float *__
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
     const int r = (int)(e / q), o = (int)(e % q) * 4;
     f32x4_t sum = *reinterpret_cast<const f32x4_t *>(part + (int64_t)r * cout + o);
+#pragma unroll 4
     for (int z = 1; z < KZ; ++z) sum += *reinterpret_cast<const f32x4_t *>(part + ((int64_t)z * cap + r) * cout + o);
     conv_bf16_epilogue<4>(sum, r, r + 1, o, cout, bias, relu, out_f32, Y);
   }
@@ -1220,9 +1250,11 @@ template <int MB>
 static void launch_bf16_wide(const void *X, int cin, const void *Wp, const float *bias, int cout, const int32_t *nbr,
                              const npvs_counts *counts, int cap, int relu, int out_f32, void *Y, hipStream_t s,
                              int KZ, float *part) {
-  int G = stride_grid(cap, 16 * MB, 4096);
-  G = (G + 7) & ~7;
-  const dim3 grid(G, (cout + 63) / 64, part ? KZ : 1);
+  const int groups = (cout + 63) / 64, split = (part ? KZ : 1) * groups;
+  // one workgroup per CU, which walks its tiles: the capacity's tiles would launch several rounds of
+  // workgroups past the sites, each with the LDS of a CU (4096 -> 64, 397 sites of 2,048: 48.5 us, 32.3 so)
+  const int G = (stride_grid(cap, 16 * (MB ? MB : 1), 256 / split > 8 ? 256 / split : 8) + 7) & ~7;
+  const dim3 grid(part ? KZ : 1, G, groups);
   conv_fwd_bf16_wide_kernel<MB><<<grid, 576, 0, s>>>((const uint16_t *)X, cin, (const bf16x8_t *)Wp, bias, cout, nbr,
                                                       counts, cap, relu, out_f32, Y, part);
   if (part)
@@ -1423,7 +1455,7 @@ npvs_status conv_fwd_dispatch(const void *X, int32_t cin, const void *Wp, const 
   if (variant == 5 || variant == 13)
     launch_bf16_wide<2>(X, cin, Wp, bias, cout, nbr, counts, cap, relu, out_f32, Y, s, KZ, part);
   else
-    launch_bf16_wide<1>(X, cin, Wp, bias, cout, nbr, counts, cap, relu, out_f32, Y, s, KZ, part);
+    launch_bf16_wide<0>(X, cin, Wp, bias, cout, nbr, counts, cap, relu, out_f32, Y, s, KZ, part);
   return check_hip(hipGetLastError(), "npvs_sparse_conv_fwd");
 }
 }  // namespace npvs
