@@ -386,7 +386,10 @@ __global__ __launch_bounds__(64 * KSPLIT) void conv_fwd_bf16_kernel(const uint16
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, uniform (scalar)
   const int kbeg = wv * KPER;
-  const int csub = 8 * (lane >> 4);
+  // wide rows are gathered by pieces (512 -> 64, 1,802 sites: 28.2 us in the product's layout, 21.4 so);
+  // one or two pieces a row are held, and the crossbar's latency shows
+  constexpr bool PIECES = KB > 2;
+  const int csub = PIECES ? piece_channel(lane) : 8 * (lane >> 4), grow = PIECES ? piece_row(lane) : lane & 15;
   for (int j = 0;; ++j) {
     const int tile = xcd_tile(blockIdx.x, gridDim.x, ntiles, j);
     if (tile < 0) break;
@@ -396,7 +399,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void conv_fwd_bf16_kernel(const uint16
 #pragma unroll
     for (int q = 0; q < KPER; ++q)
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) idx[q][mb] = nbr_index(nbr, cap, kbeg + q, row0 + mb * 16 + (lane & 15), n);
+      for (int mb = 0; mb < MB; ++mb) idx[q][mb] = nbr_index(nbr, cap, kbeg + q, row0 + mb * 16 + grow, n);
     bool act[KPER];
 #pragma unroll
     for (int q = 0; q < KPER; ++q) {
@@ -423,11 +426,15 @@ __global__ __launch_bounds__(64 * KSPLIT) void conv_fwd_bf16_kernel(const uint16
       }
       if (st >= 0 && act[st / KB]) {
         const int slot = st % PD;
+        bf16x8_t row[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+          row[mb] = PIECES ? row_operand(__builtin_bit_cast(uint4, bx[slot][mb]), lane) : bx[slot][mb];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
           for (int mb = 0; mb < MB; ++mb)
-            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[slot][nb], bx[slot][mb], acc[mb][nb], 0, 0, 0);
+            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[slot][nb], row[mb], acc[mb][nb], 0, 0, 0);
       }
     }
     if constexpr (KSPLIT == 1) {
@@ -480,7 +487,7 @@ __device__ __forceinline__ void conv_bf16_wide_body(const uint16_t *__restrict__
   const int ntiles = (n + ROWS - 1) / ROWS;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, uniform (scalar)
-  const int kbeg = wv * KPER, csub = 8 * (lane >> 4);
+  const int kbeg = wv * KPER, csub = piece_channel(lane);
   const int KB = (cin + 31) / 32, NBT = (cout + 15) / 16, nb0 = 4 * blockIdx.z;
   // input-channel split (gridDim.x > 1 only with `part`): this workgroup's 32-channel chunks
   const int KBZ = (KB + gridDim.x - 1) / gridDim.x, kb_lo = blockIdx.x * KBZ;
@@ -496,7 +503,7 @@ __device__ __forceinline__ void conv_bf16_wide_body(const uint16_t *__restrict__
 #pragma unroll
     for (int q = 0; q < KPER; ++q)
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) idx[q][mb] = nbr_index(nbr, cap, kbeg + q, row0 + mb * 16 + (lane & 15), n);
+      for (int mb = 0; mb < MB; ++mb) idx[q][mb] = nbr_index(nbr, cap, kbeg + q, row0 + mb * 16 + piece_row(lane), n);
     f32x4_t acc[MB][4];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -524,11 +531,14 @@ __device__ __forceinline__ void conv_bf16_wide_body(const uint16_t *__restrict__
     for (int g = 0; g < S; g += PD) {
 #pragma unroll
       for (int p = 0; p < PD; ++p) {
+        bf16x8_t row[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) row[mb] = row_operand(__builtin_bit_cast(uint4, bx[p][mb]), lane);
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
           for (int mb = 0; mb < MB; ++mb)
-            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[p][nb], bx[p][mb], acc[mb][nb], 0, 0, 0);
+            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[p][nb], row[mb], acc[mb][nb], 0, 0, 0);
         load(g + p + PD, p);
       }
     }

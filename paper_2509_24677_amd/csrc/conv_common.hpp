@@ -21,6 +21,19 @@ __device__ __forceinline__ int xcd_tile(int i, int G, int ntiles, int j) {
   return t < ntiles ? t : -1;
 }
 
+// Rows gathered by whole 64-byte pieces: lane l loads 16 bytes l % 4 of row l / 4 (four neighbouring
+// lanes a row; 26 cycles of the load unit where the product's own layout, neighbouring lanes on different
+// rows, takes 67), and row_operand moves them to the lanes the product reads (lane l: 16 bytes l / 16 of
+// row l % 16) through the LDS crossbar.
+__device__ __forceinline__ int piece_row(int lane) { return lane >> 2; }
+__device__ __forceinline__ int piece_channel(int lane) { return 8 * (lane & 3); }
+__device__ __forceinline__ bf16x8_t row_operand(uint4 v, int lane) {
+  const int from = 4 * (4 * (lane & 15) + (lane >> 4));
+  return __builtin_bit_cast(
+      bf16x8_t, make_uint4(__builtin_amdgcn_ds_bpermute(from, v.x), __builtin_amdgcn_ds_bpermute(from, v.y),
+                           __builtin_amdgcn_ds_bpermute(from, v.z), __builtin_amdgcn_ds_bpermute(from, v.w)));
+}
+
 __device__ __forceinline__ bf16x8_t gather8(const uint16_t *__restrict__ X, int cin, int i, int c) {
   const bool ok = i >= 0 && c < cin;
   const uint4 v = *reinterpret_cast<const uint4 *>(X + (ok ? (int64_t)i * cin + c : 0));
