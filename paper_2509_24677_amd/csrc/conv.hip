@@ -477,13 +477,15 @@ __global__ __launch_bounds__(64 * KSPLIT) void conv_fwd_bf16_kernel(const uint16
 // gather zeros, so every MFMA is unconditional (no branch around an accumulator).  The 9 partial
 // sums are added in LDS in wave order, as in the split kernel.
 // ------------------------------------------------------------------------------------------
-template <int MB>
+// NBW: blocks of 16 outputs, 4, or 2 where no more are left of the workgroup's 64 (512 -> 32, 1,802 sites:
+// 34.2 us with four, half of them repeats, 27.0 with two; 4,915 sites 46.9 and 39.1).
+template <int MB, int NBW>
 __device__ __forceinline__ void conv_bf16_wide_body(const uint16_t *__restrict__ X, int cin,
                                                     const bf16x8_t *__restrict__ Wp, const float *__restrict__ bias,
                                                     int cout, const int32_t *__restrict__ nbr, int n, int cap, int relu,
                                                     int out_f32, void *__restrict__ Y, float *__restrict__ part,
                                                     f32x4_t *__restrict__ red) {
-  constexpr int KSPLIT = 9, KPER = 3, ROWS = 16 * MB, NBLK = MB * 4, PD = MB > 2 ? 2 : 4;
+  constexpr int KSPLIT = 9, KPER = 3, ROWS = 16 * MB, NBLK = MB * NBW, PD = MB > 2 ? 2 : 4;
   const int ntiles = (n + ROWS - 1) / ROWS;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, uniform (scalar)
@@ -504,12 +506,12 @@ __device__ __forceinline__ void conv_bf16_wide_body(const uint16_t *__restrict__
     for (int q = 0; q < KPER; ++q)
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) idx[q][mb] = nbr_index(nbr, cap, kbeg + q, row0 + mb * 16 + piece_row(lane), n);
-    f32x4_t acc[MB][4];
+    f32x4_t acc[MB][NBW];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    bf16x8_t bx[PD][MB], aw[PD][4];
+      for (int nb = 0; nb < NBW; ++nb) acc[mb][nb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    bf16x8_t bx[PD][MB], aw[PD][NBW];
     // operands of stage st (clamped to the last one; zero rows past the end)
     auto load = [&](int st, int slot) {
       const bool live = st < S;
@@ -521,7 +523,7 @@ __device__ __forceinline__ void conv_bf16_wide_body(const uint16_t *__restrict__
         bx[slot][mb] = gather8(X, cin, live ? i : -1, kb * 32 + csub);
       }
 #pragma unroll
-      for (int nb = 0; nb < 4; ++nb) {
+      for (int nb = 0; nb < NBW; ++nb) {
         const int g = nb0 + nb < NBT ? nb0 + nb : NBT - 1;  // blocks past cout: any valid fragment
         aw[slot][nb] = W[(((int64_t)(kbeg + q) * NBT + g) * KB + kb) * 64 + lane];
       }
@@ -535,7 +537,7 @@ __device__ __forceinline__ void conv_bf16_wide_body(const uint16_t *__restrict__
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) row[mb] = row_operand(__builtin_bit_cast(uint4, bx[p][mb]), lane);
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
+        for (int nb = 0; nb < NBW; ++nb)
 #pragma unroll
           for (int mb = 0; mb < MB; ++mb)
             acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[p][nb], row[mb], acc[mb][nb], 0, 0, 0);
@@ -546,12 +548,12 @@ __device__ __forceinline__ void conv_bf16_wide_body(const uint16_t *__restrict__
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int nb = 0; nb < 4; ++nb) red[(wv * NBLK + mb * 4 + nb) * 64 + lane] = acc[mb][nb];
+      for (int nb = 0; nb < NBW; ++nb) red[(wv * NBLK + mb * NBW + nb) * 64 + lane] = acc[mb][nb];
     __syncthreads();
     for (int blk = wv; blk < NBLK; blk += KSPLIT) {
       f32x4_t sum = red[blk * 64 + lane];
       for (int w = 1; w < KSPLIT; ++w) sum += red[(w * NBLK + blk) * 64 + lane];
-      const int mb = blk / 4, nb = blk % 4;
+      const int mb = blk / NBW, nb = blk % NBW;
       const int r = row0 + mb * 16 + (lane & 15), o = (nb0 + nb) * 16 + 4 * (lane >> 4);
       if (part) {  // raw partial sum of this channel range; the finishing kernel adds the ranges
         if (r < n && o < cout) *reinterpret_cast<f32x4_t *>(part + ((int64_t)blockIdx.x * cap + r) * cout + o) = sum;
@@ -579,18 +581,29 @@ __global__ __launch_bounds__(576) void conv_fwd_bf16_wide_kernel(const uint16_t 
                                                                   float *__restrict__ part) {
   __shared__ f32x4_t red[9 * (MB ? MB : 4) * 4 * 64];
   const int32_t n = counts->n_sites;
+  const bool half = cout - 64 * (int)blockIdx.z <= 32;
+  auto body = [&](auto mb, auto nbw) {
+    conv_bf16_wide_body<mb.value, nbw.value>(X, cin, Wp, bias, cout, nbr, n, cap, relu, out_f32, Y, part, red);
+  };
+  constexpr std::integral_constant<int, 1> one{};
+  constexpr std::integral_constant<int, 2> two{};
+  constexpr std::integral_constant<int, 4> four{};
   if constexpr (MB > 0) {
-    conv_bf16_wide_body<MB>(X, cin, Wp, bias, cout, nbr, n, cap, relu, out_f32, Y, part, red);
+    body(std::integral_constant<int, MB>{}, four);
   } else {
     const int split = gridDim.x * gridDim.z, t = (n + 15) / 16;
     const int c1 = 2 * ((t * split + 255) / 256), c2 = 3 * (((t + 1) / 2 * split + 255) / 256),
               c4 = 4 * (((t + 3) / 4 * split + 255) / 256);
-    if (c1 <= c2 && c1 <= c4)
-      conv_bf16_wide_body<1>(X, cin, Wp, bias, cout, nbr, n, cap, relu, out_f32, Y, part, red);
-    else if (c2 <= c4)
-      conv_bf16_wide_body<2>(X, cin, Wp, bias, cout, nbr, n, cap, relu, out_f32, Y, part, red);
-    else
-      conv_bf16_wide_body<4>(X, cin, Wp, bias, cout, nbr, n, cap, relu, out_f32, Y, part, red);
+    if (c1 <= c2 && c1 <= c4) {
+      if (half) body(one, two);
+      else body(one, four);
+    } else if (c2 <= c4) {
+      if (half) body(two, two);
+      else body(two, four);
+    } else {
+      if (half) body(four, two);
+      else body(four, four);
+    }
   }
 }
 
