@@ -1404,7 +1404,15 @@ npvs_status conv_fwd_dispatch(const void *X, int32_t cin, const void *Wp, const 
     return fail(NPVS_ERR_UNSUPPORTED, "npvs_sparse_conv_fwd: BF16 needs cin % 8 == 0 and cout % 8 == 0");
   const int KB = (cin + 31) / 32, NB = (cout + 15) / 16;
   if (variant == 15) {  // variant 14 with dedicated reducer waves: at most 64 inputs and outputs
-    // (row indices are 24 bits there)
+    // (row indices are 24 bits there).  At most 32 inputs and 32 outputs: the single-role shape of 32
+    // outputs, two workgroups of which fit a CU, while the staged copies cost the same however few
+    // channels a row has (8 -> 8, us, staged / single-role: 9,175 sites 5.3 / 5.0, 52,428 12.7 / 10.1,
+    // 115,343 24.1 / 18.2; 32 -> 32 5.5 / 5.5, 13.3 / 11.1, 25.5 / 20.3).  With 33 to 48 outputs that
+    // shape takes two groups of workgroups: 24 -> 40 5.5 / 7.0, 13.4 / 18.0, 25.6 / 34.6.
+    if (KB == 1 && NB <= 2) {
+      launch_bf16_wsta<1, 1>(X, cin, Wp, bias, cout, nbr, counts, cap, relu, out_f32, Y, s);
+      return check_hip(hipGetLastError(), "npvs_sparse_conv_fwd");
+    }
     if (KB <= 2 && NB <= 4 && cap < (1 << 24)) {
       int G = 256;
       const int most = stride_grid(cap, 16, 4096);
