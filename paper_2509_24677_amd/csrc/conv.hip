@@ -491,7 +491,7 @@ __device__ __forceinline__ void conv_bf16_wide_body(const uint16_t *__restrict__
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, uniform (scalar)
   const int kbeg = wv * KPER, csub = piece_channel(lane);
   const int KB = (cin + 31) / 32, NBT = (cout + 15) / 16, nb0 = 4 * blockIdx.z;
-  // input-channel split (gridDim.x > 1 only with `part`): this workgroup's 32-channel chunks
+  // input-channel split (gridDim.x > 1 only with `part`): this workgroup's 32-channel chunks, at least one
   const int KBZ = (KB + gridDim.x - 1) / gridDim.x, kb_lo = blockIdx.x * KBZ;
   const int nkb = KB - kb_lo < KBZ ? KB - kb_lo : KBZ;
   const int S = KPER * nkb;  // stages of this wave
@@ -1370,13 +1370,16 @@ extern "C" npvs_status npvs_pack_weights_batch(int32_t n, const npvs_pack_desc *
 namespace npvs {
 // Dispatch of the BF16 kernel on (ceil(cin/32), ceil(cout/16)); MB = 2 rows blocks per wave,
 // offsets split three ways.
-// Input-channel split of the general BF16 kernel: 1, or a divisor-friendly count for 1024+ input
-// channels (8 chunks of 32 channels per split at least, at most 16 splits).
+// Input-channel split of the general BF16 kernel: 1, or the number of ranges for 1024+ input channels
+// (at most 16, of ceil(KB / wanted) chunks of 32 channels each but the last).  The ranges are counted from
+// their length, so that none is empty: 16 wanted ranges of 129 chunks have 9 chunks each, which 15 ranges
+// cover.  A workgroup of an empty range would divide by its chunk count of zero and, where the count is
+// negative, address weights past the last offset's.
 int splitk_factor(int32_t cin, int32_t cout, int32_t dtype) {
   const int KB = (cin + 31) / 32;
   if (dtype != NPVS_BF16 || KB < 32 || cin % 8 || cout % 8) return 1;
-  const int kz = KB / 8;
-  return kz > 16 ? 16 : kz;
+  const int wanted = KB / 8 > 16 ? 16 : KB / 8, len = (KB + wanted - 1) / wanted;
+  return (KB + len - 1) / len;
 }
 
 size_t conv_fwd_ws_bytes(int32_t cin, int32_t cout, int32_t cap, int32_t dtype) {
