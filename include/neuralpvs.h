@@ -238,7 +238,8 @@ npvs_status npvs_pack_weights_batch(int32_t n, const npvs_pack_desc *descs, int3
  *   output block (at most 64 outputs) in one workgroup, so a gathered row serves all outputs (more
  *   than 64 outputs: variant 12); variant 15 is variant 14 with three more waves that only sum
  *   the other waves' partial products and store the tile, while those go on to the next tile
- *   (at most 64 inputs and outputs; other shapes take variant 14).  Channel counts no tuned shape covers use a general kernel
+ *   (at most 64 inputs and outputs, fewer than 2^24 rows, X 16-byte aligned; else variant 14; at
+ *   most 32 inputs and 32 outputs: variant 12).  Channel counts no tuned shape covers use a general kernel
  *   (variants 5 and 13 select its 32-row tiles), except 65 to 160 inputs, which take the
  *   weight-stationary kernel with 16-row tiles unless variant 5 is asked for.  All variants give
  *   results within float32 rounding of each other; each one is deterministic.  Ignored by the

@@ -1416,7 +1416,9 @@ npvs_status conv_fwd_dispatch(const void *X, int32_t cin, const void *Wp, const 
       launch_bf16_wsta<1, 1>(X, cin, Wp, bias, cout, nbr, counts, cap, relu, out_f32, Y, s);
       return check_hip(hipGetLastError(), "npvs_sparse_conv_fwd");
     }
-    if (KB <= 2 && NB <= 4 && cap < (1 << 24)) {
+    // The copies to LDS take rows at 16-byte boundaries only; rows that lie between (a slice of a buffer
+    // from an odd element on) take variant 14, whose loads to registers read from any address.
+    if (KB <= 2 && NB <= 4 && cap < (1 << 24) && (reinterpret_cast<uintptr_t>(X) & 15) == 0) {
       int G = 256;
       const int most = stride_grid(cap, 16, 4096);
       if (G > most) G = (most + 7) & ~7;
