@@ -175,7 +175,7 @@ __device__ __forceinline__ void conv_f32_body(float4 *lds, const float *__restri
         left[u] = ix.i[u] >= 0 && row0 + 16 * u + (lane >> 2) < n ? cin - ix.c : 0;
         const float *src = X + (left[u] > 0 ? (int64_t)ix.i[u] * cin + ix.c : 0);
         if constexpr (ACC != kF32Any) {
-          x[u] = *reinterpret_cast<const float4 *>(src);
+          __builtin_memcpy(&x[u], src, sizeof(x[u]));  // one load, at any word's address
         } else {
           x[u].x = src[0];
           x[u].y = src[lane_mask(left[u] > 1) & 1u];
@@ -336,7 +336,9 @@ static void launch_conv_f32(const float *X, int cin, const float *P, const float
                             const npvs_counts *counts, int cap, int relu, float *Y, hipStream_t s) {
   const int64_t units = (int64_t)((cap + 15) / 16) * ((cout + 16 * NI - 1) / (16 * NI));
   const int G = units > 2048 ? 2048 : (int)((units + 7) & ~7);
-  const bool vec = cin % 4 == 0 && cout % NI == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+  // by the channel counts alone: the number of waves is the order of the sums, which X's address may not
+  // change (an unaligned 16-byte load is one instruction too)
+  const bool vec = cin % 4 == 0 && cout % NI == 0;
   // 4 waves (three workgroups a compute unit hide each other's start and end), or 8 from 256 input
   // channels on, where a wave's chain is long and the sites are few (512 -> 64, 1 802 rows: 80 us
   // against 104; 64 -> 64, 94 371 rows: 232 against 211)

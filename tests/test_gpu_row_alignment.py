@@ -30,3 +30,17 @@ def test_bf16_rows(sites, cin, cout):
     assert bool(torch.isfinite(want).all())
     for by in (1, 2, 4):
         assert torch.equal(fwd(shifted(X, by)), want), by
+
+
+@pytest.mark.parametrize("sites", [1, 300, 9000])
+@pytest.mark.parametrize("cin,cout", [(16, 64), (64, 33), (256, 64), (260, 64), (512, 16), (512, 20)])
+def test_f32_rows(sites, cin, cout):
+    rb, _ = rulebook(sites, sites)
+    gen = torch.Generator(device=DEV).manual_seed(cin * 100 + cout)
+    X = rows(sites, cin, rb.cap, gen)
+    Wp = npvs.pack_weights(torch.randn((27, cin, cout), generator=gen, device=DEV), npvs.NPVS_F32)
+    fwd = lambda x: npvs.sparse_conv_fwd(x, Wp, None, cin, cout, rb, npvs.NPVS_F32, False)[:sites]
+    want = fwd(X)
+    assert bool(torch.isfinite(want).all())
+    for by in (1, 2, 3):
+        assert torch.equal(fwd(shifted(X, by)), want), by
