@@ -92,9 +92,9 @@ __global__ void pack_batch_kernel(PackBatch PB, int dtype) {
 //   D: lane l holds the 4 NI consecutive outputs from 4 NI g on of row l%16
 // The gathered rows go through LDS (wave-private, two buffers) because the operand layout puts
 // adjacent lanes on different rows, which loads at 67 cycles a KB against 26 with four adjacent
-// lanes on one row's 64 bytes.  LDS serves a wave's accesses in order, and lane 0 writes and reads
-// the same words, so the compiler keeps their order too.  Rows are loaded two substeps ahead,
-// indices three, weights one.
+// lanes on one row's 64 bytes.  LDS serves a wave's accesses in order, and a wave-scope fence per substep
+// (no instruction) keeps the compiler to it.  Rows are loaded two substeps ahead, indices three,
+// weights one.
 // Bound by the matrix cores: the busiest compute unit of the 9 699-row 64 -> 64 layer has 1 296
 // products of 32 cycles per SIMD, 17 us of its 32.6 (113 us with vector FMA; without any load the
 // same loop takes 25), the rest being the launch and the first index, row and weight round trips.
@@ -232,6 +232,9 @@ __device__ __forceinline__ void conv_f32_body(float4 *lds, const float *__restri
     // substep s (parity cur): its rows are in LDS, those of the next in x[cur ^ 1], indices two ahead in ix
     auto step = [&](auto parity) {
       constexpr int cur = decltype(parity)::value;
+      // the rows stored at the end of the step before come before this step's reads of them, and the
+      // reads of the step before come before this step's store: of other lanes' words, so said here
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
       load_rows(ix, x[cur], xl[cur]);
       ix = next_index();
       load_weights(w[cur ^ 1], wl[cur ^ 1]);
