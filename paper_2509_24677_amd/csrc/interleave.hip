@@ -258,6 +258,10 @@ __global__ __launch_bounds__(256) void deinterleave_threshold_kernel(Batch B, in
 // eight froxels stores two 16-byte words 32 bytes apart).  Bound by the logits' store (a plain fill of
 // their 33.6 MB takes 5.7 us for a city frame): 13.2 us by bytes, 12.3 so, 10.9 with the store past the
 // caches, which the logits of a frame do not fit.  Two or four items a thread: 11.8 and 12.1.
+// At d = 4 four lines in y and two in z read one 128-byte line of Y, which is read once only if their froxels
+// are pieces (a workgroup's 1,024 froxels) of one XCD.  RUN: consecutive pieces that go to one XCD; 0: an
+// eighth of all pieces, which have a workgroup each.
+template <int RUN>
 __global__ __launch_bounds__(256) void deinterleave_logits_kernel(Batch B, int64_t total_bytes,
                                                                    const float *__restrict__ Y, int C,
                                                                    const int32_t *__restrict__ block_row,
@@ -267,12 +271,20 @@ __global__ __launch_bounds__(256) void deinterleave_logits_kernel(Batch B, int64
   typedef float F4 __attribute__((ext_vector_type(4)));
   const int d = B.d, ld = __builtin_ctz(d);
   const float ninf = -__builtin_huge_valf();
-  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < 2 * total_bytes;
-       u += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t t = u >> 1;
-    const int half = (int)u & 1;
+  const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+  int piece = xcd * (int)(gridDim.x / 8) + slot;
+  if constexpr (RUN > 0) piece = (slot / RUN * 8 + xcd) * RUN + slot % RUN;
+  for (int64_t u0 = 256 * (int64_t)piece; u0 < 2 * total_bytes; u0 += 256 * (int64_t)gridDim.x) {
+    // the grid of the workgroup's first byte, by halves over scalar loads; of the others too where no
+    // grid ends between (a walk per lane waits for one line of kernel arguments a grid)
     int b = 0;
-    while (b + 1 < B.n && t >= B.g[b + 1].occ_off) ++b;
+    for (int s = NPVS_MAX_GRIDS / 2; s; s >>= 1)
+      if (b + s < B.n && (u0 >> 1) >= B.g[b + s].occ_off) b += s;
+    const int64_t u = u0 + threadIdx.x, t = u >> 1;
+    if (u >= 2 * total_bytes) break;
+    const int half = (int)u & 1;
+    if (b + 1 < B.n && ((u0 + 255) >> 1) >= B.g[b + 1].occ_off)
+      while (b + 1 < B.n && t >= B.g[b + 1].occ_off) ++b;
     const GridDesc &g = B.g[b];
     // 32-bit index arithmetic: a grid holds at most 1024^3 / 8 bytes
     const uint32_t l = (uint32_t)(t - g.occ_off), rb = (uint32_t)g.nx >> 3, ny = (uint32_t)g.ny;
@@ -367,8 +379,19 @@ extern "C" npvs_status npvs_deinterleave_threshold(const float *Y, int32_t y_str
   const int C = d * d * d, stride = y_stride ? y_stride : C;
   if (stride < C) return fail(NPVS_ERR_INVALID_ARG, "npvs_deinterleave_threshold: y_stride below d^3");
   if (logits && d >= 4 && stride % 4 == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0) {
-    deinterleave_logits_kernel<<<stride_grid(2 * total, 256, 8192), 256, 0, as_stream(stream)>>>(
-        B, total, Y, stride, block_row, occ_bits, pvs_bits, logits);
+    // An eighth of the pieces per XCD while each has a workgroup: the lines that share a row of Y then lie in
+    // one eighth whatever the extents are.  Larger batches are walked in steps of 8,192 pieces, in runs of 16,
+    // which hold the four lines of y up to nx = 1,024 and keep the steps' reads close together.  d = 4, every
+    // block active, us, in runs of 1 / 16 / an eighth of the (step's) pieces, bytes' kernel in brackets: sixteen
+    // 96 x 64 x 64 19.8 / 15.5 / 12.6 (17.5), 192 x 192 x 128 15.8 / 13.2 / 10.0 (14.6), a city frame 16.6 /
+    // 20.2 / 16.4 (17.1), 512^3 387 / 322 / 350 (332), 1024 x 512 x 256 704 / 342 / 385 (425).
+    const int64_t pieces = (2 * total + 255) / 256;
+    if (pieces <= 8192)
+      deinterleave_logits_kernel<0><<<(pieces + 7) & ~7, 256, 0, as_stream(stream)>>>(B, total, Y, stride, block_row,
+                                                                                      occ_bits, pvs_bits, logits);
+    else
+      deinterleave_logits_kernel<16><<<8192, 256, 0, as_stream(stream)>>>(B, total, Y, stride, block_row, occ_bits,
+                                                                          pvs_bits, logits);
     return check_hip(hipGetLastError(), "npvs_deinterleave_threshold");
   }
   int grid = stride_grid(total, 256, 8192);
