@@ -909,14 +909,16 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 // A workgroup barrier that orders LDS only: unlike __syncthreads it does not wait for loads in flight.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <int KB>
+// NBLK: output blocks of 16, 3 or 4.  With three, each reducer has one, and the
+// fourth's products and partial sums, a repeat, are left out (24 -> 40, 115,343 sites: 25.6 us with four, 22.4).
+template <int KB, int NBLK>
 __global__ __launch_bounds__(768) void conv_fwd_bf16_wsred_kernel(const uint16_t *__restrict__ X, int cin,
                                                                   const bf16x8_t *__restrict__ Wp,
                                                                   const float *__restrict__ bias, int cout,
                                                                   const int32_t *__restrict__ nbr,
                                                                   const npvs_counts *__restrict__ counts, int cap,
                                                                   int relu, int out_f32, void *__restrict__ Y) {
-  constexpr int KSPLIT = 9, KPER = 3, ROWS = 16, NBLK = 4, NRED = 3;
+  constexpr int KSPLIT = 9, KPER = 3, ROWS = 16, NRED = 3;
   constexpr int RING = 8, IDX = 512;  // ring slots; the 27 x 16 indices of a step, three loads of 64 a reducer
   typedef RowStage<KB> S;
   __shared__ f32x4_t red[2][KSPLIT * NBLK * 64];
@@ -1416,7 +1418,7 @@ npvs_status conv_fwd_dispatch(const void *X, int32_t cin, const void *Wp, const 
     // outputs, two workgroups of which fit a CU, while the staged copies cost the same however few
     // channels a row has (8 -> 8, us, staged / single-role: 9,175 sites 5.3 / 5.0, 52,428 12.7 / 10.1,
     // 115,343 24.1 / 18.2; 32 -> 32 5.5 / 5.5, 13.3 / 11.1, 25.5 / 20.3).  With 33 to 48 outputs that
-    // shape takes two groups of workgroups: 24 -> 40 5.5 / 7.0, 13.4 / 18.0, 25.6 / 34.6.
+    // shape takes two groups of workgroups: 24 -> 40 5.5 / 7.4, 11.8 / 17.7, 22.4 / 33.9.
     if (KB == 1 && NB <= 2) {
       launch_bf16_wsta<1, 1>(X, cin, Wp, bias, cout, nbr, counts, cap, relu, out_f32, Y, s);
       return check_hip(hipGetLastError(), "npvs_sparse_conv_fwd");
@@ -1427,12 +1429,13 @@ npvs_status conv_fwd_dispatch(const void *X, int32_t cin, const void *Wp, const 
       int G = 256;
       const int most = stride_grid(cap, 16, 4096);
       if (G > most) G = (most + 7) & ~7;
-      if (KB == 1)
-        conv_fwd_bf16_wsred_kernel<1><<<dim3(G, 1), 768, 0, s>>>((const uint16_t *)X, cin, (const bf16x8_t *)Wp,
-                                                                 bias, cout, nbr, counts, cap, relu, out_f32, Y);
-      else
-        conv_fwd_bf16_wsred_kernel<2><<<dim3(G, 1), 768, 0, s>>>((const uint16_t *)X, cin, (const bf16x8_t *)Wp,
-                                                                 bias, cout, nbr, counts, cap, relu, out_f32, Y);
+      auto launch = [&](auto kernel) {
+        kernel<<<dim3(G, 1), 768, 0, s>>>((const uint16_t *)X, cin, (const bf16x8_t *)Wp, bias, cout, nbr, counts, cap,
+                                          relu, out_f32, Y);
+      };
+      if (KB == 2) launch(conv_fwd_bf16_wsred_kernel<2, 4>);
+      else if (NB == 4) launch(conv_fwd_bf16_wsred_kernel<1, 4>);
+      else launch(conv_fwd_bf16_wsred_kernel<1, 3>);
       return check_hip(hipGetLastError(), "npvs_sparse_conv_fwd");
     }
     variant = 14;
