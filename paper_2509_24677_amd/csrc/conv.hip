@@ -837,8 +837,10 @@ __device__ __forceinline__ void wsta_body(const uint16_t *__restrict__ X, int ci
   if constexpr (FUSE) write_db_parts();
 }
 
+// At most six waves a SIMD: with one input chunk two of the nine-wave workgroups then fit a compute unit, as
+// the launch counts on, and not three, which leaves others one (32 -> 4096, 9,700 sites: 225 us with three, 200 with two).
 template <int KB, int MB, int NBW = 2>
-__global__ __launch_bounds__(576) void conv_fwd_bf16_wsta_kernel(const uint16_t *__restrict__ X, int cin,
+__global__ __launch_bounds__(576) __attribute__((amdgpu_waves_per_eu(3, 6))) void conv_fwd_bf16_wsta_kernel(const uint16_t *__restrict__ X, int cin,
                                                                   const bf16x8_t *__restrict__ Wp,
                                                                   const float *__restrict__ bias, int cout,
                                                                   const int32_t *__restrict__ nbr,
