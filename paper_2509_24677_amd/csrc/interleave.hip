@@ -158,16 +158,16 @@ __global__ __launch_bounds__(256) void gather_bits_kernel(Batch B, const uint8_t
                                                            const npvs_counts *__restrict__ counts, T *__restrict__ X,
                                                            int stride, const uint8_t *__restrict__ bits2,
                                                            uint8_t *__restrict__ X2) {
-  const int d = B.d;
+  const int d = B.d, ld = __builtin_ctz(d);  // a power of two: shifts where the arithmetic is most of the work
   const int32_t n = counts->n_sites;
   const int64_t runs = (int64_t)n * d * d;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < runs; t += (int64_t)gridDim.x * blockDim.x) {
-    int oy = t % d, oz = (t / d) % d;
-    int32_t r = (int32_t)(t / ((int64_t)d * d));
-    int32_t key = site_keys[r];
+    const int oy = (int)t & (d - 1), oz = (int)(t >> ld) & (d - 1);
+    const int32_t r = (int32_t)(t >> (2 * ld));
+    const int32_t key = site_keys[r];
     const BlockGrid g = block_grid(B, grid_of_key(B, key));
-    int32_t l = key - g.key_off;
-    int bx = l % g.Bx, by = (l / g.Bx) % g.By, bz = l / (g.Bx * g.By);
+    const int32_t l = key - g.key_off, q = l / g.Bx;
+    const int bx = l - q * g.Bx, by = q % g.By, bz = q / g.By;
     const int64_t row_off = g.occ_off + ((int64_t)(bz * d + oz) * g.ny + (by * d + oy)) * (g.nx >> 3);
     const uint8_t *row = bits + row_off;
     T *dst = X + (int64_t)r * stride + (oz * d + oy) * d;
