@@ -363,9 +363,9 @@ __device__ __forceinline__ uint32_t frox_row(const TriSetup &S, int xa, int xb, 
 // Bound by latency: a row is a search of TRIS offsets in LDS, a PVS load and a short test, twelve of
 // them a triangle, and all of a workgroup's triangles are set up by one wave first.  256 triangles a
 // workgroup left most CUs one workgroup or none (50,000 triangles in a city frame: 196, 50.3 us; 13.3
-// now; 200 triangles 19.8 and 6.5 us, 1,000,000 188 and 117 us).
-template <int TRIS>
-__global__ __launch_bounds__(256) void visible_tris_kernel(const float *__restrict__ tris, Batch B, int64_t total,
+// now).
+template <int TRIS, int THREADS>
+__global__ __launch_bounds__(THREADS) void visible_tris_kernel(const float *__restrict__ tris, Batch B, int64_t total,
                                                             const uint8_t *__restrict__ pvs, int words,
                                                             uint8_t *__restrict__ visible) {
   __shared__ TriSetup srec[TRIS];
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(256) void visible_tris_kernel(const float *__restri
     __syncthreads();
     const int R = row0[TRIS];
     const int n = total - base < TRIS ? (int)(total - base) : TRIS;
-    for (int r = tid; r < R; r += 256) {
+    for (int r = tid; r < R; r += THREADS) {
       int lo = 0, hi = n - 1;  // last staged triangle whose rows start at or before r
       while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -725,21 +725,26 @@ extern "C" npvs_status npvs_visible_triangles(const float *tris, const int64_t *
   // whole aligned PVS words: every x extent a multiple of 32 and an aligned grid
   bool words = (reinterpret_cast<uintptr_t>(pvs_bits) & 3) == 0;
   for (int b = 0; b < n_grids; ++b) words = words && dims[b].nx % 32 == 0;
-  // Triangles a workgroup: few while workgroups are few, more as setup and staging count.  Measured in
-  // city scenes (us, 16 / 32 / 48 / 64 a workgroup): 8,000 triangles 8.7 / 9.6 / 12.0 / 13.6; 20,000
-  // 12.9 / 9.9 / 12.4 / 14.7; 50,000 21.4 / 15.8 / 13.7 / 15.7; 200,000 68 / 44 / 37.4 / 38.2; 1,000,000
-  // 340 / 211 / 171 / 158.
-  auto launch = [&](auto kernel, int tris_per_wg) {
-    kernel<<<stride_grid(total, tris_per_wg, 8192), 256, 0, as_stream(stream)>>>(tris, B, total, pvs_bits, words, visible);
+  // Triangles a workgroup: few while workgroups are few, more as setup and staging count; from 65,537 on half
+  // the threads too, as a workgroup lives about 5 us whatever its rows are and the chip is full.  Measured on a
+  // 256 x 256 x 128 grid (us): scattered 8-froxel triangles, many rows each, with 16 / 32 / 48 / 64 a workgroup
+  // of 256 and 64 of 128: 8,000 13.0 / 15.9 / 20.9 / 23.7 / 36.7, 20,000 15.1 / 17.9 / 21.5 / 24.7 / 40.6,
+  // 50,000 26.4 / 26.0 / 26.1 / 27.6 / 39.5, 200,000 76 / 67 / 65 / 66 / 75, 1,000,000 359 / 286 / 268 / 250 /
+  // 248; scattered about a grid of half the extents, few or none: 8,000 5.9 / 5.8 / 5.8 / 5.8 / 5.8, 50,000
+  // 10.7 / 8.3 / 6.3 / 6.1 / 6.1, 100,000 17.6 / 11.9 / 10.1 / 9.1 / 6.9, 200,000 30.7 / 19.4 / 15.3 / 13.4 /
+  // 10.3, 1,000,000 156 / 91 / 66 / 51 / 38.  256 a workgroup: 78.8, 76.9, 78.9, 144 and 430; 9.4, 7.4, 8.6,
+  // 13.0 and 43.
+  auto launch = [&](auto kernel, int tris_per_wg, int threads) {
+    kernel<<<stride_grid(total, tris_per_wg, 8192), threads, 0, as_stream(stream)>>>(tris, B, total, pvs_bits, words, visible);
   };
   if (total <= 10000)
-    launch(visible_tris_kernel<16>, 16);
+    launch(visible_tris_kernel<16, 256>, 16, 256);
   else if (total <= 32768)
-    launch(visible_tris_kernel<32>, 32);
-  else if (total <= 300000)
-    launch(visible_tris_kernel<48>, 48);
+    launch(visible_tris_kernel<32, 256>, 32, 256);
+  else if (total <= 65536)
+    launch(visible_tris_kernel<48, 256>, 48, 256);
   else
-    launch(visible_tris_kernel<64>, 64);
+    launch(visible_tris_kernel<64, 128>, 64, 128);
   return check_hip(hipGetLastError(), "npvs_visible_triangles");
 }
 
