@@ -138,10 +138,15 @@ __device__ __forceinline__ bool quantize_tri(const float *__restrict__ tris, int
   return empty;
 }
 
-// LDS table of the tiles one workgroup appends to (open addressing on the tile index).
-// Twice the tiles that 256 scattered triangles meet: with 512 entries, nearly full, searches of
-// hundreds of entries held one workgroup of a batch for 20,000 cycles (6,000 now).
+// LDS table of the tiles one workgroup appends to (open addressing on the tile index): all of it where more
+// than kBinWide of the 256 triangles meet more than two tiles, else the first half, which costs less to go
+// through (20 triangles 13.5 -> 12.9 us, a city frame 32.3 -> 32.0).  256 scattered triangles of two tiles meet
+// about half as many tiles as the whole table holds; up to 2,048 are possible.  An append that finds no entry
+// in kBinProbes goes straight to the tile's counter: with 512 entries, nearly full, and no such limit,
+// searches of hundreds of entries held one workgroup of a batch for 20,000 cycles, and scattered 8-froxel
+// triangles (2,000 in 256 x 256 x 128) take 282 us so, 37.6 with the limit and 27.4 with the whole table.
 constexpr int kBinSlots = 1024;
+constexpr int kBinWide = 48;
 constexpr int kBinProbes = 16;
 // Tile counters lie 16 bytes apart: updates that share a line come one after the other (a city frame's
 // wait for them 12,500 -> 9,700 cycles).
@@ -182,7 +187,6 @@ __global__ __launch_bounds__(256) void frox_bin_kernel(const float *__restrict__
   __shared__ int htile[kBinSlots];
   __shared__ int hcount[kBinSlots];
   __shared__ int hbase[kBinSlots];
-  __shared__ int kept[kBinKeep][256];  // table entry and slot << 16 of a thread's appends; < 0: none
   __shared__ __align__(16) TriSetup srec[256];
   for (int i = threadIdx.x; i < kBinSlots; i += blockDim.x) {
     htile[i] = -1;
@@ -219,7 +223,11 @@ __global__ __launch_bounds__(256) void frox_bin_kernel(const float *__restrict__
   // ignored triangles: one counter update per wave that has any
   const uint64_t badm = __ballot(bad);
   if (n_ignored && badm && (threadIdx.x & 63) == 0) atomicAdd(n_ignored, (int)__popcll(badm));
+  __shared__ int wide[4];  // triangles of each wave that meet more than two tiles
+  const int wide_mine = (int)__popcll(__ballot(ntl > 2));
+  if ((threadIdx.x & 63) == 0) wide[threadIdx.x >> 6] = wide_mine;
   __syncthreads();  // the table is initialized
+  const int slots = wide[0] + wide[1] + wide[2] + wide[3] > kBinWide ? kBinSlots : kBinSlots / 2;
   // Appends are counted per workgroup first: each (triangle, tile) takes a local slot from the
   // tile's entry in the LDS table, then one global counter update per (workgroup, tile) reserves
   // the entry's range.  Consecutive triangles mostly share tiles, so a tile that hundreds of
@@ -240,30 +248,45 @@ __global__ __launch_bounds__(256) void frox_bin_kernel(const float *__restrict__
     if (slot < kFroxTileCap) tile_list[(int64_t)tile * kFroxTileCap + slot] = (int32_t)t;
   };
   // an append that reserved its slot alone lists the chunks it starts itself
-  auto direct = [&](int tile) {
-    const int slot = atomicAdd(&tile_count[tile * kCountStride], 1);
+  auto place = [&](int tile, int slot) {
     append(tile, slot);
     if (chunks) {
       const int k = chunks_started(slot, 1);
       if (k) write_chunks(tile, slot, 1, chunks, atomicAdd(n_chunks, k));
     }
   };
-  for (int j = 0; j < kBinKeep && j < ntl; ++j, step()) {
+  int kept[kBinKeep];  // table entry and slot << 16 of this thread's appends; < 0: none
+#pragma unroll
+  for (int j = 0; j < kBinKeep; ++j) {
+    kept[j] = -1;
+    if (j >= ntl) continue;
     const int tile = tile_here();
-    int h = (int)(((uint32_t)tile * 2654435761u) >> 22) & (kBinSlots - 1), v = -1;
-    for (int probe = 0; probe < kBinProbes; ++probe, h = (h + 1) & (kBinSlots - 1)) {
-      // a plain read first: lanes share it, where exchanges of one word come one lane at a time
-      int cur = *(volatile int *)&htile[h];
-      if (cur == -1) cur = atomicCAS(&htile[h], -1, tile);
+    int h = (int)(((uint32_t)tile * 2654435761u) >> 22) & (slots - 1);
+    for (int probe = 0; probe < kBinProbes; ++probe, h = (h + 1) & (slots - 1)) {
+      const int cur = atomicCAS(&htile[h], -1, tile);
       if (cur == -1 || cur == tile) {
-        v = h | atomicAdd(&hcount[h], 1) << 16;
+        kept[j] = h | atomicAdd(&hcount[h], 1) << 16;
         break;
       }
     }
-    kept[j][threadIdx.x] = v;
-    if (v < 0) direct(tile);
+    if (kept[j] < 0) place(tile, atomicAdd(&tile_count[tile * kCountStride], 1));
+    step();
   }
-  for (int j = kBinKeep; j < ntl; ++j, step()) direct(tile_here());  // large triangles: the rest directly
+  // large triangles: the rest directly, four updates in flight (one after the other, 20 triangles over a grid of
+  // 128^3 took 450 us, 300 so)
+  for (int j = kBinKeep; j < ntl; j += 4) {
+    int tile[4], slot[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (j + q < ntl) {
+        tile[q] = tile_here();
+        slot[q] = atomicAdd(&tile_count[tile[q] * kCountStride], 1);
+        step();
+      }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (j + q < ntl) place(tile[q], slot[q]);
+  }
   __syncthreads();
   // one counter update per table entry, then the chunks the workgroup's ranges start: one update
   // of the chunk count for the whole workgroup
@@ -273,12 +296,12 @@ __global__ __launch_bounds__(256) void frox_bin_kernel(const float *__restrict__
 #pragma unroll
   for (int u = 0; u < kBinSlots / 256; ++u) {  // all updates in flight before the first answer
     const int i = threadIdx.x + 256 * u;
-    if (htile[i] >= 0) first[u] = atomicAdd(&tile_count[htile[i] * kCountStride], hcount[i]);
+    if (256 * u < slots && htile[i] >= 0) first[u] = atomicAdd(&tile_count[htile[i] * kCountStride], hcount[i]);
   }
 #pragma unroll
   for (int u = 0; u < kBinSlots / 256; ++u) {
     const int i = threadIdx.x + 256 * u;
-    if (htile[i] >= 0) {
+    if (256 * u < slots && htile[i] >= 0) {
       hbase[i] = first[u];
       if (chunks) nch[u] = chunks_started(first[u], hcount[i]);
     }
@@ -314,10 +337,9 @@ __global__ __launch_bounds__(256) void frox_bin_kernel(const float *__restrict__
     }
   }
   __syncthreads();
-  for (int j = 0; j < kBinKeep && j < ntl; ++j) {
-    const int v = kept[j][threadIdx.x], ent = v & (kBinSlots - 1);
-    if (v >= 0) append(htile[ent], hbase[ent] + (v >> 16));
-  }
+#pragma unroll
+  for (int j = 0; j < kBinKeep; ++j)
+    if (kept[j] >= 0) append(htile[kept[j] & (kBinSlots - 1)], hbase[kept[j] & (kBinSlots - 1)] + (kept[j] >> 16));
   // the records last and in whole lines (written when the counters' barriers had passed)
   const int64_t t0 = (int64_t)blockIdx.x * 256;
   const int words = (int)(total - t0 < 256 ? total - t0 : 256) * kRecWords;
