@@ -69,7 +69,7 @@ def conv_traffic(variant):
     elif variant == 14:
         name = "conv_fwd_bf16_wsta_kernel<2, 1, 4>"
     elif variant == 15:
-        name = "conv_fwd_bf16_wsred_kernel<2>"
+        name = "conv_fwd_bf16_wsred_kernel<2, 4>"
     else:
         name = f"conv_fwd_bf16_wsta_kernel<2, {variant - 11}, 2>"
     for line in text.splitlines():
@@ -1149,7 +1149,7 @@ def main():
     shapes = {0: "<2,4,1,9>", 1: "<2,4,2,1>", 2: "<2,4,1,3>", 3: "<2,4,2,3>", 4: "<2,4,1,1>", 5: "<2,4,2,9>",
               6: "_lds<2,4,1,4>", 7: "_lds<2,4,1,2>", 8: "_lds<2,4,2,2>", 9: "_lds<2,4,1,8>",
               10: "_lds<2,4,2,4>", 11: "_lds<2,4,2,8>", 12: "_wsta<2,1>", 13: "_wsta<2,2>", 14: "_wsta<2,1,4>",
-              15: "_wsred<2>"}
+              15: "_wsred<2, 4>"}
     alg_bytes = n_sites * 64 * 2 * 2 + 27 * n_sites * 4 + 27 * 64 * 64 * 2  # X in, Y out, neighbour map, weights
     roofline = {"bound": "mfma", "achieved": achieved, "peak": BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / BF16_PEAK_TFLOPS, "traffic": conv_traffic(net_b.variant[1]),

@@ -222,9 +222,9 @@ npvs_status npvs_pack_weights_batch(int32_t n, const npvs_pack_desc *descs, int3
 /* ---------------------------------------------------------------------------------------------
  * Submanifold sparse 3x3x3 convolution, forward (Sec. 2.3, 3.3):
  *   Y[r][o] = act(bias[o] + sum_k sum_c X[nbr[k][r]][c] W[k][c][o]),  act = ReLU if relu.
- * dtype NPVS_F32: X, Y float32, vector FMA.  dtype NPVS_BF16: X bfloat16, products on MFMA
- * with float32 accumulation, bias and ReLU in float32; Y is bfloat16, or float32 when
- * out_f32 = 1 (the logits of the last layer).
+ * dtype NPVS_F32: X, Y float32, products and sums in float32 on the matrix cores.  dtype
+ * NPVS_BF16: X bfloat16, products on MFMA with float32 accumulation, bias and ReLU in float32; Y
+ * is bfloat16, or float32 when out_f32 = 1 (the logits of the last layer).
  *   X (device) [cap_sites][cin]; Wp packed weights; bias (device, nullable) float32 [cout];
  *   nbr, counts from npvs_build_rulebook; Y (device) [cap_sites][cout], rows >= n_sites untouched.
  * BF16 requires cin % 8 == 0 and cout % 8 == 0 (NPVS_ERR_UNSUPPORTED otherwise).

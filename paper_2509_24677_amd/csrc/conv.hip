@@ -80,7 +80,7 @@ __global__ void pack_batch_kernel(PackBatch PB, int dtype) {
 
 // ------------------------------------------------------------------------------------------
 // FP32 path on MFMA (v_mfma_f32_16x16x4_f32: float32 operands and accumulation), any channel
-// counts.  A workgroup of NW waves computes 16 MB rows x 16 NI outputs; the contraction over
+// counts; the order of a sum follows from the channel counts alone.  A workgroup of NW waves computes 16 MB rows x 16 NI outputs; the contraction over
 // (offset, input channel) is cut into substeps of 16 channels of one offset, dealt to the waves in
 // turn, so a wave's rows and weights are its own and nothing is shared (no barrier) until the NW
 // partial results are added in LDS in a fixed order.  The product is computed transposed
@@ -483,7 +483,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void conv_fwd_bf16_kernel(const uint16
 // sums are added in LDS in wave order, as in the split kernel.
 // ------------------------------------------------------------------------------------------
 // NBW: blocks of 16 outputs, 4, or 2 where no more are left of the workgroup's 64 (512 -> 32, 1,802 sites:
-// 34.2 us with four, half of them repeats, 27.0 with two; 4,915 sites 46.9 and 39.1).
+// 34.2 us with four, half of them repeats, 23.8 with two; 4,915 sites 46.9 and 34.0).
 template <int MB, int NBW>
 __device__ __forceinline__ void conv_bf16_wide_body(const uint16_t *__restrict__ X, int cin,
                                                     const bf16x8_t *__restrict__ Wp, const float *__restrict__ bias,
@@ -587,11 +587,12 @@ __device__ __forceinline__ void conv_bf16_wide_body(const uint16_t *__restrict__
 
 // MB = 1, 2 or 4 blocks of 16 rows per workgroup (equal sums either way); 0: by the number of sites.
 // A workgroup reads all its weights once per tile, so more rows a tile read them less often, but fewer
-// tiles leave CUs idle.  A round of 256 workgroups measured 20, 31 and 41 us for MB = 1, 2 and 4 (4096 ->
-// 64 in 16 ranges), hence the least of 2, 3 and 4 times the rounds.  The range is blockIdx.x, so that
-// ranges go to XCDs in turn and an XCD's L2 holds the weights of its own two of 16 (14 MB in all; 40
-// sites 47.2 us with a range's tiles over all XCDs, 22.9 so).  One block a tile before and this, 4096 -> 64, us: 397 sites
-// 50.8 -> 32.3, 1,024 88.8 -> 48.4, 2,048 162.5 -> 92.5; 1024 -> 128, 1,802 sites 85.2 -> 46.8.
+// tiles leave CUs idle.  A round of 256 workgroups measured 23, 31 and 44 us for MB = 1, 2 and 4 (4096 ->
+// 64 in 16 ranges, with the finishing launch), hence the least of 2, 3 and 4 times the rounds.  The range is
+// blockIdx.x, so that ranges go to XCDs in turn and an XCD's L2 holds the weights of its own two of 16 (14 MB
+// in all; 40 sites 47.2 us with a range's tiles over all XCDs, 21.6 so).  One block a tile before and this,
+// 4096 -> 64, us: 397 sites 50.8 -> 31.3, 1,024 88.8 -> 43.8, 2,048 162.5 -> 82.5; 1024 -> 128, 1,802 sites
+// 85.2 -> 42.3.
 template <int MB>
 __global__ __launch_bounds__(576) void conv_fwd_bf16_wide_kernel(const uint16_t *__restrict__ X, int cin,
                                                                   const bf16x8_t *__restrict__ Wp,
@@ -928,7 +929,7 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // NBLK: output blocks of 16, 3 or 4.  With three, each reducer has one, and the
-// fourth's products and partial sums, a repeat, are left out (24 -> 40, 115,343 sites: 25.6 us with four, 22.4).
+// fourth's products and partial sums, a repeat, are left out (24 -> 40, 115,343 sites: 24.2 us with four, 21.4).
 template <int KB, int NBLK>
 __global__ __launch_bounds__(768) void conv_fwd_bf16_wsred_kernel(const uint16_t *__restrict__ X, int cin,
                                                                   const bf16x8_t *__restrict__ Wp,
@@ -1300,7 +1301,9 @@ static void launch_bf16_wide(const void *X, int cin, const void *Wp, const float
                              int KZ, float *part) {
   const int groups = (cout + 63) / 64, split = (part ? KZ : 1) * groups;
   // one workgroup per CU, which walks its tiles: the capacity's tiles would launch several rounds of
-  // workgroups past the sites, each with the LDS of a CU (4096 -> 64, 397 sites of 2,048: 48.5 us, 32.3 so)
+  // workgroups past the sites, each with the LDS of a CU (4096 -> 64, 397 sites of 2,048: 48.5 us, 31.3 so).
+  // At least eight tiles are walked at once (one per XCD), so that more than 32 ranges times groups, such as
+  // 4096 -> 512 or 168 -> 4096, do take several rounds.
   const int G = (stride_grid(cap, 16 * (MB ? MB : 1), 256 / split > 8 ? 256 / split : 8) + 7) & ~7;
   const dim3 grid(part ? KZ : 1, G, groups);
   conv_fwd_bf16_wide_kernel<MB><<<grid, 576, 0, s>>>((const uint16_t *)X, cin, (const bf16x8_t *)Wp, bias, cout, nbr,
@@ -1393,8 +1396,6 @@ extern "C" npvs_status npvs_pack_weights_batch(int32_t n, const npvs_pack_desc *
 }
 
 namespace npvs {
-// Dispatch of the BF16 kernel on (ceil(cin/32), ceil(cout/16)); MB = 2 rows blocks per wave,
-// offsets split three ways.
 // Input-channel split of the general BF16 kernel: 1, or the number of ranges for 1024+ input channels
 // (at most 16, of ceil(KB / wanted) chunks of 32 channels each but the last).  The ranges are counted from
 // their length, so that none is empty: 16 wanted ranges of 129 chunks have 9 chunks each, which 15 ranges
@@ -1412,6 +1413,7 @@ size_t conv_fwd_ws_bytes(int32_t cin, int32_t cout, int32_t cap, int32_t dtype) 
   return kz > 1 ? sizeof(float) * (size_t)kz * cap * cout : 0;
 }
 
+// Dispatch by type, variant and (ceil(cin / 32), ceil(cout / 16)).
 npvs_status conv_fwd_dispatch(const void *X, int32_t cin, const void *Wp, const float *bias, int32_t cout,
                               const int32_t *nbr, const npvs_counts *counts, int32_t cap, int32_t dtype, int32_t relu,
                               int32_t out_f32, void *Y, hipStream_t s, int variant, void *ws, size_t ws_bytes) {
@@ -1434,9 +1436,9 @@ npvs_status conv_fwd_dispatch(const void *X, int32_t cin, const void *Wp, const 
   if (variant == 15) {  // variant 14 with dedicated reducer waves: at most 64 inputs and outputs
     // (row indices are 24 bits there).  At most 32 inputs and 32 outputs: the single-role shape of 32
     // outputs, two workgroups of which fit a CU, while the staged copies cost the same however few
-    // channels a row has (8 -> 8, us, staged / single-role: 9,175 sites 5.3 / 5.0, 52,428 12.7 / 10.1,
-    // 115,343 24.1 / 18.2; 32 -> 32 5.5 / 5.5, 13.3 / 11.1, 25.5 / 20.3).  With 33 to 48 outputs that
-    // shape takes two groups of workgroups: 24 -> 40 5.5 / 7.4, 11.8 / 17.7, 22.4 / 33.9.
+    // channels a row has (8 -> 8, us, staged / single-role: 9,175 sites 5.3 / 4.7, 52,428 12.7 / 9.3,
+    // 115,343 24.1 / 16.0; 32 -> 32 5.5 / 4.9, 13.3 / 10.0, 25.5 / 18.1).  With 33 to 48 outputs that
+    // shape takes two groups of workgroups: 24 -> 40 4.8 / 6.4, 11.4 / 15.8, 21.4 / 29.6.
     if (KB == 1 && NB <= 2) {
       launch_bf16_wsta<1, 1>(X, cin, Wp, bias, cout, nbr, counts, cap, relu, out_f32, Y, s);
       return check_hip(hipGetLastError(), "npvs_sparse_conv_fwd");

@@ -1,4 +1,4 @@
-// Device helpers shared by the BF16 convolution kernels (conv.hip, stack.hip).
+// Device helpers shared by the BF16 convolution kernels (conv.hip).
 #pragma once
 
 #include "npvs_common.hpp"

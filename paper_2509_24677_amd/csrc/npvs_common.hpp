@@ -69,7 +69,7 @@ __device__ __forceinline__ BlockGrid block_grid(const Batch &B, int b) {
 // ------------------------------------------------------------------------------------------
 // bfloat16: raw uint16 bit patterns.  float -> bf16 rounds to nearest, ties to even (NaN stays a
 // quiet NaN), two values at a time in one instruction (v_cvt_pk_bf16_f32; the integer form of the
-// same rounding, equal on all 2^32 inputs, takes about eight per value).
+// same rounding takes about eight per value).
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t f32x2_to_bf16(float lo, float hi) {
   typedef float f32x2_t __attribute__((ext_vector_type(2)));
